@@ -1455,14 +1455,9 @@ __global__ __launch_bounds__(kBlock) void k_ep_finalize(EpArgs a0) {
   }
 }
 
-// Seeds of the backward sweep at the endpoints: constrained required times, and the
-// adjoint of the smoothed objective with respect to each endpoint's smoothed arrival.
-// Seeds of the endpoints list[0..n) (every endpoint when list is NULL and n = E).
-__global__ __launch_bounds__(kBlock) void k_ep_seed(EpArgs a0, const int* __restrict__ list, int n) {
-  const int t = (int)(blockIdx.x * kBlock + threadIdx.x);
-  if (t >= n) return;
-  const int i = list ? list[t] : t;
-  const EpArgs a = ep_snap(a0);
+// Seed of the backward sweep at endpoint i: its constrained required times, and the adjoint of
+// the smoothed objective with respect to its smoothed arrival.
+__device__ __forceinline__ void ep_seed(const EpArgs& a, int i) {
   const int e = a.ep_sslot ? a.ep_sslot[i] : a.ep_pin[i];   // the endpoint's workspace slot
   a.sink[rat_at(e)] = make_float4(a.hold, a.hold, a.rat_late, a.rat_late);
   if (a.seed_adj) {
@@ -1483,6 +1478,13 @@ __global__ __launch_bounds__(kBlock) void k_ep_seed(EpArgs a0, const int* __rest
     const float sc = a.scale_dev ? a.scale * (float)a.scale_dev[0] : a.scale;
     a.sink[adj_at(e)] = make_float4(-sc * coef * ev.w0, -sc * coef * ev.w1, 0.f, 0.f);
   }
+}
+
+// Seeds of the endpoints list[0..n) (every endpoint when list is NULL and n = E).
+__global__ __launch_bounds__(kBlock) void k_ep_seed(EpArgs a0, const int* __restrict__ list, int n) {
+  const int t = (int)(blockIdx.x * kBlock + threadIdx.x);
+  if (t >= n) return;
+  ep_seed(ep_snap(a0), list ? list[t] : t);
 }
 
 // Under checkpointing: the values of the endpoints list[0..n), taken while their nets'
@@ -1533,6 +1535,8 @@ __global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
   float2* atg_out = snap_elems(a.atg, a.snap.pins);
   GroupSlot gs;
   if (!group_slot(a.range, gs) || !gs.active) return;
+  // Plain stores: scattered streaming ones in original order took 94 us for 841k pins, these 35 us.
+  auto put = [](auto* p, const auto& v) { *p = v; };
   const int n = a.sched[gs.entry];
   const int p0 = a.net_off[n], p1 = a.net_off[n + 1];
   const float4 c0 = rec[kRecChunks * (size_t)n], c1 = rec[kRecChunks * (size_t)n + 1],
@@ -1542,11 +1546,11 @@ __global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
   for (int p = p0 + gs.gl; p < p1; p += gs.G) {
     const float2 w = wire[p];
     const int q = a.io_perm ? a.io_perm[p] : p;
-    if (at_out) store_stream(at_out + q, make_float4(at.x + w.x, at.y + w.x, at.z + w.x, at.w + w.x));
+    if (at_out) put(at_out + q, make_float4(at.x + w.x, at.y + w.x, at.z + w.x, at.w + w.x));
     if (slew_out)
-      store_stream(slew_out + q,
+      put(slew_out + q,
                    make_float4(sink_slew(sl.x, w.y), sink_slew(sl.y, w.y), sink_slew(sl.z, w.y), sink_slew(sl.w, w.y)));
-    if (atg_out) store_stream(atg_out + q, make_float2(ag.x + w.x, ag.y + w.x));
+    if (atg_out) put(atg_out + q, make_float2(ag.x + w.x, ag.y + w.x));
   }
 }
 
@@ -1582,7 +1586,9 @@ struct BwdArgs {
 };
 
 // Accumulators of the net step (reduced over the group).
-enum { R_E0, R_E1, R_L0, R_L1, A_R, A_F, S_R, S_F, X_RS, X_N, Y_RS, Y_N, N_ACC };
+// The driver's slew adjoint is its slew times Q: d slew(sink) / d slew(driver) is their ratio, and
+// the sinks hold their slew adjoint already divided by their own slew.
+enum { R_E0, R_E1, R_L0, R_L1, A_R, A_F, Q_R, Q_F, X_RS, X_N, Y_RS, Y_N, N_ACC, S_R = Q_R, S_F = Q_F };
 
 struct SinkKeep {     // what phase 3 needs of a sink, kept in registers
   float gx, gy, rest;
@@ -1599,11 +1605,12 @@ struct SinkIn {
 };
 
 // Sink p, whose workspace slot is `slot` (its pin without checkpointing).
-template <bool kCanon, bool kGrad>
+template <bool kCanon, bool kGrad, bool kRat = true>
 __device__ __forceinline__ SinkIn sink_load(const BwdArgs& a, int p, int slot) {
   SinkIn in;
   const uint32_t u = (uint32_t)p;
-  in.rt = ld(a.sink, rat_at((uint32_t)slot));
+  in.rt = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (kRat) in.rt = ld(a.sink, rat_at((uint32_t)slot));
   in.w = ld(a.wire, (uint32_t)slot);
   in.q = kCanon ? p : ld(a.io_perm, u);
   in.aj = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1617,46 +1624,31 @@ __device__ __forceinline__ SinkIn sink_load(const BwdArgs& a, int p, int slot) {
   return in;
 }
 
-// Net step of one sink: per-pin outputs and its contribution to the driver's reductions.
+// Net step of one sink: its contribution to the driver's reductions, and what its own wire
+// adjoint needs.
 template <bool kGrad>
-__device__ __forceinline__ SinkKeep sink_step(const BwdArgs& a, const SinkIn& in, const float4& at_d,
-                                              const float4& sl_d, float xd, float yd, float (&acc)[N_ACC],
-                                              bool write, int pc) {
+__device__ __forceinline__ SinkKeep sink_sum(const BwdArgs& a, const SinkIn& in, float xd, float yd,
+                                             float (&acc)[N_ACC], bool write, int pc) {
   const float4 rt = in.rt, aj = in.aj;
   const float2 w = in.w;
-  const int q = in.q;
-  const float xs = in.xs, ys = in.ys, cp = in.cp;
-  const float4 ats = make_float4(at_d.x + w.x, at_d.y + w.x, at_d.z + w.x, at_d.w + w.x);
-  const float4 sls = make_float4(sink_slew(sl_d.x, w.y), sink_slew(sl_d.y, w.y), sink_slew(sl_d.z, w.y),
-                                 sink_slew(sl_d.w, w.y));
-  if (write) {
-    const uint32_t uq = (uint32_t)q;
-    if (a.at_out) store_stream(at32(a.at_out, uq), ats);
-    if (a.slew_out) store_stream(at32(a.slew_out, uq), sls);
-    if (a.rat_out) store_stream(at32(a.rat_out, uq), rt);
-    if (a.slack_out)
-      store_stream(at32(a.slack_out, uq), make_float4(ats.x - rt.x, ats.y - rt.y, rt.z - ats.z, rt.w - ats.w));
-  }
   acc[R_E0] = fmaxf(acc[R_E0], rt.x - w.x);
   acc[R_E1] = fmaxf(acc[R_E1], rt.y - w.x);
   acc[R_L0] = fminf(acc[R_L0], rt.z - w.x);
   acc[R_L1] = fminf(acc[R_L1], rt.w - w.x);
-  SinkKeep k{0.f, 0.f, 0.f, q};
+  SinkKeep k{0.f, 0.f, 0.f, in.q};
   if (kGrad) {
-    const float q0 = sls.z > 0.f ? aj.z * frcp(sls.z) : 0.f;   // s_bar(s,t) / slew(s,late,t)
-    const float q1 = sls.w > 0.f ? aj.w * frcp(sls.w) : 0.f;
     acc[A_R] += aj.x;
     acc[A_F] += aj.y;
-    acc[S_R] += q0 * sl_d.z;
-    acc[S_F] += q1 * sl_d.w;
+    acc[Q_R] += aj.z;                                    // s_bar(s,t) / slew(s,late,t)
+    acc[Q_F] += aj.w;
     const float dbar = aj.x + aj.y;                      // adjoint of the wire delay
-    const float ibar = (q0 + q1) * w.y;                  // adjoint of the impulse
+    const float ibar = (aj.z + aj.w) * w.y;              // adjoint of the impulse
     if (a.tree_adj && write) *at32(a.tree_adj, (uint32_t)pc) = make_float2(dbar, ibar);
-    const float len = fabsf(xs - xd) + fabsf(ys - yd);
+    const float len = fabsf(in.xs - xd) + fabsf(in.ys - yd);
     // d Delay / d len = d Impulse / d len = 1e-3 r (Cpin + c len) for a star sink.
-    k.rest = (dbar + ibar) * (1e-3f * a.r * fmaf(a.c, len, cp));
-    k.gx = sgnf(xs - xd);
-    k.gy = sgnf(ys - yd);
+    k.rest = (dbar + ibar) * (1e-3f * a.r * fmaf(a.c, len, in.cp));
+    k.gx = sgnf(in.xs - xd);
+    k.gy = sgnf(in.ys - yd);
     acc[X_RS] += k.gx * k.rest;
     acc[X_N] += k.gx;
     acc[Y_RS] += k.gy * k.rest;
@@ -1665,11 +1657,36 @@ __device__ __forceinline__ SinkKeep sink_step(const BwdArgs& a, const SinkIn& in
   return k;
 }
 
+// The same with its per-pin outputs.
+template <bool kGrad>
+__device__ __forceinline__ SinkKeep sink_step(const BwdArgs& a, const SinkIn& in, const float4& at_d,
+                                              const float4& sl_d, float xd, float yd, float (&acc)[N_ACC],
+                                              bool write, int pc) {
+  const float4 rt = in.rt;
+  const float2 w = in.w;
+  if (write) {
+    const float4 ats = make_float4(at_d.x + w.x, at_d.y + w.x, at_d.z + w.x, at_d.w + w.x);
+    const uint32_t uq = (uint32_t)in.q;
+    if (a.at_out) store_stream(at32(a.at_out, uq), ats);
+    if (a.slew_out)
+      store_stream(at32(a.slew_out, uq), make_float4(sink_slew(sl_d.x, w.y), sink_slew(sl_d.y, w.y),
+                                                     sink_slew(sl_d.z, w.y), sink_slew(sl_d.w, w.y)));
+    if (a.rat_out) store_stream(at32(a.rat_out, uq), rt);
+    if (a.slack_out)
+      store_stream(at32(a.slack_out, uq), make_float4(ats.x - rt.x, ats.y - rt.y, rt.z - ats.z, rt.w - ats.w));
+  }
+  return sink_sum<kGrad>(a, in, xd, yd, acc, write, pc);
+}
+
 struct ArcBwd {         // one arc of the cell step, seen from one condition's lane
-  float d, xg, s, ddx, ddy, dsx, dsy;
+  float d, xg, s, ddx, ddy, dsx, dsy;   // ddx, dsx divided by the input slew (see inv_slew)
   int pin, tp, slot;
   bool valid;
 };
+
+// The partials that lead to the input slew, divided by it: the sinks' slew adjoints are kept
+// that way.  A slew of zero passes no adjoint on.
+__device__ __forceinline__ float inv_slew(float slew) { return slew > 0.f ? frcp(slew) : 0.f; }
 
 __device__ __forceinline__ ArcBwd arc_backward(const BwdArgs& a, const Slots& sl, int kc, int j, int m, int t,
                                                float load) {
@@ -1683,12 +1700,13 @@ __device__ __forceinline__ ArcBwd arc_backward(const BwdArgs& a, const Slots& sl
   r.xg = -kInf;
   if (in.valid) {
     const LutVal v = lut_eval<true>(a.grid, a.coef, a.keys, in.arc, t, in.slew, load);
+    const float rs = inv_slew(in.slew);
     r.d = v.d;
     r.s = v.s;
     r.xg = in.atg + v.d;
-    r.ddx = v.ddx;
+    r.ddx = v.ddx * rs;
     r.ddy = v.ddy;
-    r.dsx = v.dsx;
+    r.dsx = v.dsx * rs;
     r.dsy = v.dsy;
   }
   return r;
@@ -1699,6 +1717,7 @@ __device__ __forceinline__ ArcBwd arc_backward(const BwdArgs& a, const Slots& sl
 // lanes without an arc come back invalid.
 __device__ __forceinline__ ArcBwd arc_from_input(const BwdArgs& a, const ArcIn& in, int t, float load) {
   const LutVal v = lut_eval<true>(a.grid, a.coef, a.keys, in.arc, t, in.slew, load);
+  const float rs = inv_slew(in.slew);
   ArcBwd r;
   r.valid = in.valid;
   r.pin = in.pin;
@@ -1707,11 +1726,27 @@ __device__ __forceinline__ ArcBwd arc_from_input(const BwdArgs& a, const ArcIn& 
   r.d = in.valid ? v.d : 0.f;
   r.s = in.valid ? v.s : 0.f;
   r.xg = in.valid ? in.atg + v.d : -kInf;
-  r.ddx = in.valid ? v.ddx : 0.f;
+  r.ddx = in.valid ? v.ddx * rs : 0.f;
   r.ddy = in.valid ? v.ddy : 0.f;
-  r.dsx = in.valid ? v.dsx : 0.f;
+  r.dsx = in.valid ? v.dsx * rs : 0.f;
   r.dsy = in.valid ? v.dsy : 0.f;
   return r;
+}
+
+// Sum of a lane's arcs, paired as the quad butterfly over four one-arc lanes pairs them, so that
+// every lane mapping of a cell gives the same bits.
+template <int NA>
+__device__ __forceinline__ float sum_arcs(const float (&v)[NA]) {
+  if constexpr (NA == 1) return v[0];
+  else if constexpr (NA == 2) return v[0] + v[1];
+  else return (v[0] + v[1]) + (v[2] + v[3]);
+}
+
+// Adjoint of the root load: uv = {U_r, U_f, V_r, V_f}, per output transition the softmax-weighted
+// d delay / d load over the arcs and d slew / d load of the worst-slew arc, times the driver's
+// adjoints.
+__device__ __forceinline__ float load_adjoint(const float4& uv, float a_r, float a_f, float s_r, float s_f) {
+  return fmaf(a_r, uv.x, fmaf(a_f, uv.y, fmaf(s_r, uv.z, s_f * uv.w)));
 }
 
 // Group-wide reduction of the net-step accumulators (G = 16/32/64 wave groups, or a whole
@@ -1783,7 +1818,7 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
   int4 e[NA];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
-    e[i] = ld(a.ell, cell_lane ? (uint32_t)(sl.base + min(jl + AL * i, sl.F - 1) * sl.nc + kc) : 0u);
+    e[i] = ld(a.ell, cell_lane ? (uint32_t)(sl.base + min(jl * NA + i, sl.F - 1) * sl.nc + kc) : 0u);
   const float load = ld(a.load, (uint32_t)n);
   const int slot = a.loc ? ld(a.loc, (uint32_t)n) : n;
   const int p1 = gs.active ? p1v : p0;
@@ -1796,7 +1831,7 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
   ArcIn ain[NA];
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
-    ain[i].valid = cell_lane && jl + AL * i < sl.F && e[i].x >= 0;
+    ain[i].valid = cell_lane && jl * NA + i < sl.F && e[i].x >= 0;
     ain[i].arc = ell_arc(e[i]);
     ain[i].tp = ell_positive(e[i]) ? t : 1 - t;
     ain[i].pin = e[i].y;
@@ -1827,7 +1862,7 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
   if (block) in1 = sink_load<kCanon, kGrad>(a, has1 ? s0 + gstride : p0, has1 ? sk0 + s0 + gstride : 0);
   __builtin_amdgcn_sched_barrier(0);          // keep wave 2 ahead of the lookup below
 
-  // 2a. Cell-step lookups (wave 3): lane (k, jl) of the cell lanes takes arcs jl + AL * i.
+  // 2a. Cell-step lookups (wave 3): lane (k, jl) of the cell lanes takes arcs jl * NA + i.
   ArcBwd arc0[NA];
 #pragma unroll
   for (int i = 0; i < NA; ++i) arc0[i] = arc_from_input(a, ain[i], t, load);
@@ -1850,12 +1885,13 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
       xmax = fmaxf(xmax, arc0[i].valid ? arc0[i].xg : -kInf);
       const bool take = arc0[i].valid && (jstar == STA_MAX_FANIN || arc0[i].s > smax);
       smax = take ? arc0[i].s : smax;
-      jstar = take ? jl + AL * i : jstar;
+      jstar = take ? jl * NA + i : jstar;
     }
     xmax = arc_reduce<kMax, AL>(xmax);
+    float ez[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) z += arc0[i].valid ? fexp((arc0[i].xg - xmax) * a.inv_gamma) : 0.f;
-    z = arc_reduce<kSum, AL>(z);
+    for (int i = 0; i < NA; ++i) ez[i] = arc0[i].valid ? fexp((arc0[i].xg - xmax) * a.inv_gamma) : 0.f;
+    z = arc_reduce<kSum, AL>(sum_arcs<NA>(ez));
   }
   arc_argmax<AL>(smax, jstar);
   for (int j0 = kArcLanes; j0 < sl.F; j0 += kArcLanes) {    // cells wider than 4 inputs
@@ -1863,21 +1899,22 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       v[i].valid = false;
-      if (cell_lane) v[i] = arc_backward(a, sl, kc, j0 + jl + AL * i, m, t, load);
+      if (cell_lane) v[i] = arc_backward(a, sl, kc, j0 + jl * NA + i, m, t, load);
     }
-    float cm = -kInf, cz = 0.f, s2 = -kInf;
+    float cm = -kInf, s2 = -kInf;
     int j2 = STA_MAX_FANIN;
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       cm = fmaxf(cm, v[i].valid ? v[i].xg : -kInf);
       const bool take = v[i].valid && (j2 == STA_MAX_FANIN || v[i].s > s2);
       s2 = take ? v[i].s : s2;
-      j2 = take ? j0 + jl + AL * i : j2;
+      j2 = take ? j0 + jl * NA + i : j2;
     }
     cm = arc_reduce<kMax, AL>(cm);
+    float ez[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) cz += v[i].valid ? fexp((v[i].xg - cm) * a.inv_gamma) : 0.f;
-    cz = arc_reduce<kSum, AL>(cz);
+    for (int i = 0; i < NA; ++i) ez[i] = v[i].valid ? fexp((v[i].xg - cm) * a.inv_gamma) : 0.f;
+    const float cz = arc_reduce<kSum, AL>(sum_arcs<NA>(ez));
     lse_merge(xmax, z, cm, cz, a.inv_gamma);
     arc_argmax<AL>(s2, j2);
     if (s2 > smax) {
@@ -1901,48 +1938,59 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
   // 2b. Cell step: required times of the inputs and the adjoint split.
   const float rat_o = k == 0 ? acc[R_E0] : (k == 1 ? acc[R_E1] : (k == 2 ? acc[R_L0] : acc[R_L1]));
   const float abar = t ? acc[A_F] : acc[A_R];
-  const float sbar = t ? acc[S_F] : acc[S_R];
+  const float sb_r = acc[Q_R] * sl_d.z, sb_f = acc[Q_F] * sl_d.w;   // slew adjoint of the driver
+  const float sbar = t ? sb_f : sb_r;
   const float inv_z = frcp(z);
-  float lb = 0.f;
+  float lu = 0.f, lv = 0.f;                    // load partials U, V of the condition's transition
   for (int j0 = 0; j0 < sl.F; j0 += kArcLanes) {
+    float u[NA], vv[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
+      u[i] = vv[i] = 0.f;
       ArcBwd v = arc0[i];
       if (j0 > 0) {
         v.valid = false;
-        if (cell_lane) v = arc_backward(a, sl, kc, j0 + jl + AL * i, m, t, load);
+        if (cell_lane) v = arc_backward(a, sl, kc, j0 + jl * NA + i, m, t, load);
       }
       if (cell_lane && v.valid) {
         // RAT(input, k') = RAT(output, k) - arc delay.
         float* sw = reinterpret_cast<float*>(a.sink);
         *at32(sw, 4 * rat_at((uint32_t)v.slot) + (uint32_t)(2 * m + v.tp)) = rat_o - v.d;
         if (kGrad && m == 1) {
-          const float dbar = fexp((v.xg - xmax) * a.inv_gamma) * inv_z * abar;   // softmax weight x adjoint
-          const float s_j = (j0 + jl + AL * i) == jstar ? sbar : 0.f;
+          const float wj = fexp((v.xg - xmax) * a.inv_gamma) * inv_z;   // softmax weight
+          const float dbar = wj * abar;
+          const bool star = (j0 + jl * NA + i) == jstar;
           const uint32_t aj = 4 * adj_at((uint32_t)v.slot);
           *at32(sw, aj + (uint32_t)v.tp) = dbar;
-          *at32(sw, aj + 2u + (uint32_t)v.tp) = fmaf(dbar, v.ddx, s_j * v.dsx);
-          lb = fmaf(dbar, v.ddy, fmaf(s_j, v.dsy, lb));
+          *at32(sw, aj + 2u + (uint32_t)v.tp) = fmaf(dbar, v.ddx, star ? sbar * v.dsx : 0.f);
+          u[i] = wj * v.ddy;
+          vv[i] = star ? v.dsy : 0.f;
         }
       }
     }
+    if (kGrad) {
+      lu += arc_reduce<kSum, AL>(sum_arcs<NA>(u));
+      lv += arc_reduce<kSum, AL>(sum_arcs<NA>(vv));
+    }
   }
 
-  // 3. Load adjoint of the root: arcs summed over the arc lanes of late rise + late fall
-  //    (cell lanes 2 * AL and 3 * AL).
+  // 3. Load adjoint of the root from the load partials of late rise and late fall (cell
+  //    lanes 2 * AL and 3 * AL).
   float lbar = 0.f;
   if (kGrad) {
-    lb = arc_reduce<kSum, AL>(lb);
+    float4 uv;
     if (!block) {
       const int base = (threadIdx.x & 63) & ~(G - 1);
-      lbar = __shfl(lb, base + 2 * AL) + __shfl(lb, base + 3 * AL);
+      uv = make_float4(__shfl(lu, base + 2 * AL), __shfl(lu, base + 3 * AL), __shfl(lv, base + 2 * AL),
+                       __shfl(lv, base + 3 * AL));
     } else {
-      if (threadIdx.x == 2 * AL) sh[0] = lb;
-      if (threadIdx.x == 3 * AL) sh[1] = lb;
+      if (threadIdx.x == 2 * AL) { sh[0] = lu; sh[2] = lv; }
+      if (threadIdx.x == 3 * AL) { sh[1] = lu; sh[3] = lv; }
       __syncthreads();
-      lbar = sh[0] + sh[1];
+      uv = make_float4(sh[0], sh[1], sh[2], sh[3]);
       __syncthreads();
     }
+    lbar = load_adjoint(uv, acc[A_R], acc[A_F], sb_r, sb_f);
   }
   if (!gs.active) return;
   if (kGrad && (a.dx || a.dy) && !a.tree_adj) {
@@ -2023,6 +2071,428 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level(int nh, int h0, int e0, in
   } else {
     if constexpr (G0 == 2) bwd_net<4, kCanon, kGrad>(a, sl, gs, sh);
   }
+}
+
+// ---------------------------------------------------------------------------- backward, split by role
+// The backward level in three roles that run side by side in one launch, on workgroups of
+// their own, instead of one after the other in the lanes of a net (k_bwd_level):
+//  * cells (pre): for the cells of the next lower level, everything of the cell step that the
+//    forward state alone decides - per input the arc delays, softmax weights and table
+//    partials - written into the inputs' own workspace slots, which are empty until the cell
+//    step fills them;
+//  * chain: the net step's reductions and the cell step as one multiply-add per input, in
+//    place in those slots: the only part that the next level waits for;
+//  * outputs (post): per-pin outputs and the Elmore adjoint, from the same sinks.
+// A level of one design holds about one wave per SIMD, so that its time is the instruction
+// chain and the dependent loads of one wave, not bytes: in one wave the lookups (three round
+// trips), reductions and outputs of a 2.5M-pin level took 5.9 us; apart, the longest role
+// bounds the launch.
+//
+// What a slot holds before and after the cell step of the cell it feeds (k' = input condition,
+// i = input transition, t the output transition that the arc's unateness pairs with it):
+//   before: {D[k']}, {+-W[i], B[i]}: arc delay; softmax weight, its sign bit set on the worst-slew
+//           arc; d delay / d slew over the sink's slew;
+//   after:  {RAT(output) - D}, {W A, W A B + (worst-slew arc: S C)}.
+// The slot of a net's driver pin, which no sink uses, holds {U_r, U_f, V_r, V_f} (load_adjoint)
+// and {C_r, C_f} (d slew / d slew over the sink's slew, of the worst-slew arc), by output
+// transition.  Every value is computed by the operations of k_bwd_level in the same order, so
+// both give the same bits.
+
+// Which net a thread serves, as level_slot, with the smallest group 2^g0 known at run time.
+struct LevelRanges {
+  int nh, h0, e0, e1, e2, e3, e4, e5, w1, w2, w3, w4, w5, g0;
+};
+__device__ __forceinline__ bool step_slot(int bx, const LevelRanges& r, GroupSlot& s) {
+  if (bx < r.nh) {
+    s.block = true;
+    s.G = kBlock;
+    s.gl = threadIdx.x;
+    s.entry = r.h0 + bx;
+    s.active = true;
+    return true;
+  }
+  s.block = false;
+  const int wave = (bx - r.nh) * kWavesPerBlock + (int)(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (wave >= r.w5) return false;
+  const int c = (wave >= r.w1) + (wave >= r.w2) + (wave >= r.w3) + (wave >= r.w4);
+  const int eb = c == 0 ? r.e0 : (c == 1 ? r.e1 : (c == 2 ? r.e2 : (c == 3 ? r.e3 : r.e4)));
+  const int ee = c == 0 ? r.e1 : (c == 1 ? r.e2 : (c == 2 ? r.e3 : (c == 3 ? r.e4 : r.e5)));
+  const int wb = c == 0 ? 0 : (c == 1 ? r.w1 : (c == 2 ? r.w2 : (c == 3 ? r.w3 : r.w4)));
+  const int lg = r.g0 + c;
+  s.G = 1 << lg;
+  s.gl = lane & (s.G - 1);
+  s.entry = eb + (wave - wb) * (64 >> lg) + (lane >> lg);
+  s.active = s.entry < ee;
+  return true;
+}
+
+// The net step's reductions that a role needs: required times (kRat) and entries [A_R, kLast).
+template <int G, bool kRat, int kLast>
+__device__ __forceinline__ void reduce_step(float (&v)[N_ACC], bool block, float* sh) {
+  if (kRat) {
+    v[R_E0] = wave_group_reduce<kMax, G>(v[R_E0]);
+    v[R_E1] = wave_group_reduce<kMax, G>(v[R_E1]);
+    v[R_L0] = wave_group_reduce<kMin, G>(v[R_L0]);
+    v[R_L1] = wave_group_reduce<kMin, G>(v[R_L1]);
+  }
+#pragma unroll
+  for (int i = A_R; i < kLast; ++i) v[i] = wave_group_reduce<kSum, G>(v[i]);
+  if (G == 64 && block) {
+    const int w = threadIdx.x >> 6;
+    constexpr int i0 = kRat ? 0 : A_R;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int i = i0; i < kLast; ++i) sh[w * N_ACC + i] = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = i0; i < kLast; ++i) {
+      float r = sh[i];
+      for (int q = 1; q < kWavesPerBlock; ++q) {
+        const float b = sh[q * N_ACC + i];
+        r = i <= R_E1 ? fmaxf(r, b) : (i <= R_L1 ? fminf(r, b) : r + b);
+      }
+      v[i] = r;
+    }
+    __syncthreads();
+  }
+}
+
+// Chain role of one net of level >= 1: two round trips of loads - {pin range, cell-input
+// slots}, then {sinks, own inputs' slots} - a reduction of at most eight values, and the
+// inputs' slots rewritten in place.  Lane j takes input j for all its conditions.
+template <int G, bool kGrad, bool kRat>
+__device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, const GroupSlot& gs, float* sh) {
+  const int gl = gs.gl;
+  const bool block = gs.block;
+  const int n = gs.active ? gs.entry : a.N0 + sl.c0;
+  const int kc = n - a.N0 - sl.c0;
+  const int p0 = ld(a.net_off, (uint32_t)n);
+  const int p1v = ld(a.net_off, (uint32_t)n + 1u);
+  const int2* ell2 = reinterpret_cast<const int2*>(a.ell);   // second half: {arc with the sign, slot}
+  const bool in0 = gs.active && gl < sl.F;
+  int2 e = ld(ell2, 2u * (uint32_t)(sl.base + (in0 ? gl * sl.nc : 0) + kc) + 1u);
+  float sl_r = 0.f, sl_f = 0.f;
+  if (kGrad) {
+    const float* rec = reinterpret_cast<const float*>(a.rec);
+    sl_r = ld(rec, 4u * (uint32_t)(kRecChunks * n + 2) + 1u);
+    sl_f = ld(rec, 4u * (uint32_t)(kRecChunks * n + 3) + 1u);
+  }
+  const int p1 = gs.active ? p1v : p0;
+  // An empty input slot of the padded layout names pin 0, the driver of net 0: no input's slot.
+  bool has = in0 && e.y != 0;
+  float4 d = make_float4(0.f, 0.f, 0.f, 0.f), wb = d;
+  float2 cst = make_float2(0.f, 0.f);
+  const int stride = block ? kBlock : G;
+  const int s0 = p0 + 1 + gl;
+  const bool h0 = s0 < p1;
+  const uint32_t u0 = h0 ? (uint32_t)s0 : 0u;
+  float4 rt = d, aj = d;
+  if (kRat) rt = ld(a.sink, rat_at(u0));
+  if (kGrad) aj = ld(a.sink, adj_at(u0));
+  const float w0 = kRat ? ld(a.wire, u0).x : 0.f;
+  if (kRat) d = ld(a.sink, rat_at((uint32_t)e.y));
+  if (kGrad) {
+    wb = ld(a.sink, adj_at((uint32_t)e.y));
+    const float4 c4 = ld(a.sink, adj_at((uint32_t)p0));
+    cst = make_float2(c4.x, c4.y);
+  }
+  float acc[N_ACC] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto take = [&](const float4& r, const float4& j, float w) {
+    if (kRat) {
+      acc[R_E0] = fmaxf(acc[R_E0], r.x - w);
+      acc[R_E1] = fmaxf(acc[R_E1], r.y - w);
+      acc[R_L0] = fminf(acc[R_L0], r.z - w);
+      acc[R_L1] = fminf(acc[R_L1], r.w - w);
+    }
+    if (kGrad) {
+      acc[A_R] += j.x;
+      acc[A_F] += j.y;
+      acc[Q_R] += j.z;
+      acc[Q_F] += j.w;
+    }
+  };
+  if (h0) take(rt, aj, w0);
+  if (block) {
+    for (int p = s0 + stride; p < p1; p += stride) {
+      const uint32_t u = (uint32_t)p;
+      float4 r2 = rt, j2 = aj;
+      if (kRat) r2 = ld(a.sink, rat_at(u));
+      if (kGrad) j2 = ld(a.sink, adj_at(u));
+      take(r2, j2, kRat ? ld(a.wire, u).x : 0.f);
+    }
+  }
+  reduce_step<G, kRat, kGrad ? X_RS : A_R>(acc, block, sh);
+  const float sc_r = kGrad ? acc[Q_R] * sl_r * cst.x : 0.f;
+  const float sc_f = kGrad ? acc[Q_F] * sl_f * cst.y : 0.f;
+  for (int j = gl; gs.active && j < sl.F; j += stride) {
+    if (j != gl) {                             // more inputs than lanes
+      e = ld(ell2, 2u * (uint32_t)(sl.base + j * sl.nc + kc) + 1u);
+      has = e.y != 0;
+      if (kRat) d = ld(a.sink, rat_at((uint32_t)e.y));
+      if (kGrad) wb = ld(a.sink, adj_at((uint32_t)e.y));
+    }
+    if (!has) break;                           // a cell's inputs fill its first slots
+    const bool flip = e.x < 0;
+    if (kRat)
+      *at32(a.sink, rat_at((uint32_t)e.y)) =
+          make_float4((flip ? acc[R_E1] : acc[R_E0]) - d.x, (flip ? acc[R_E0] : acc[R_E1]) - d.y,
+                      (flip ? acc[R_L1] : acc[R_L0]) - d.z, (flip ? acc[R_L0] : acc[R_L1]) - d.w);
+    if (kGrad) {
+      const float d_r = fabsf(wb.x) * (flip ? acc[A_F] : acc[A_R]);
+      const float d_f = fabsf(wb.y) * (flip ? acc[A_R] : acc[A_F]);
+      const float s_r = __builtin_signbit(wb.x) ? (flip ? sc_f : sc_r) : 0.f;
+      const float s_f = __builtin_signbit(wb.y) ? (flip ? sc_r : sc_f) : 0.f;
+      *at32(a.sink, adj_at((uint32_t)e.y)) = make_float4(d_r, d_f, fmaf(d_r, wb.z, s_r), fmaf(d_f, wb.w, s_f));
+    }
+  }
+}
+
+// Outputs role of one net: the net step again, for its per-pin outputs, and the Elmore adjoint.
+// The driver's part of an output follows its sinks' at once, so that streaming stores (`stream`,
+// see stream_outputs) leave L2 with whole lines: 2.6M pins in canonical order with every output
+// take 84 us with plain stores (368 MB, 4.4 TB/s), 103 us with streaming ones, and 134 us with
+// streaming ones when the driver's part comes after the reductions.
+template <int G, bool kGrad, bool kRat>
+__device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, bool stream, float* sh) {
+  const int gl = gs.gl;
+  const bool block = gs.block;
+  const int n = gs.active ? gs.entry : 0;
+  const int p0 = ld(a.net_off, (uint32_t)n);
+  const int p1v = ld(a.net_off, (uint32_t)n + 1u);
+  const uint32_t rs = (uint32_t)(kRecChunks * n);
+  const float4 c0 = ld(a.rec, rs), c1 = ld(a.rec, rs + 1), c2 = ld(a.rec, rs + 2), c3 = ld(a.rec, rs + 3);
+  const float4 at_d = make_float4(c0.x, c1.x, c2.x, c3.x);
+  const float4 sl_d = make_float4(c0.y, c1.y, c2.y, c3.y);
+  const int p1 = gs.active ? p1v : p0;
+  const bool canon = a.io_perm == nullptr;
+  const uint32_t qd = canon ? (uint32_t)p0 : (uint32_t)ld(a.io_perm, (uint32_t)p0);
+  float xd = 0.f, yd = 0.f;
+  float4 uv = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (kGrad) {
+    xd = ld(a.x, qd);
+    yd = ld(a.y, qd);
+    if (n >= a.N0) uv = ld(a.sink, rat_at((uint32_t)p0));
+  }
+  const int stride = block ? kBlock : G;
+  const int s0 = p0 + 1 + gl;
+  const bool has0 = s0 < p1, has1 = block && s0 + stride < p1;
+  auto load = [&](int p) {
+    return canon ? sink_load<true, kGrad, kRat>(a, p, p) : sink_load<false, kGrad, kRat>(a, p, p);
+  };
+  const SinkIn in0 = load(has0 ? s0 : p0);
+  SinkIn in1{};
+  if (block) in1 = load(has1 ? s0 + stride : p0);
+  auto put = [&](float4* out, uint32_t q, const float4& v) {
+    if (!out) return;
+    if (stream) store_stream(at32(out, q), v);
+    else *at32(out, q) = v;
+  };
+  auto arrive = [&](uint32_t q, const float4& at, const float4& sl) {
+    put(a.at_out, q, at);
+    put(a.slew_out, q, sl);
+  };
+  auto require = [&](uint32_t q, const float4& at, const float4& rt) {
+    put(a.rat_out, q, rt);
+    put(a.slack_out, q, make_float4(at.x - rt.x, at.y - rt.y, rt.z - at.z, rt.w - at.w));
+  };
+  auto sink_at = [&](const SinkIn& in) {
+    return make_float4(at_d.x + in.w.x, at_d.y + in.w.x, at_d.z + in.w.x, at_d.w + in.w.x);
+  };
+  auto sink_arrive = [&](const SinkIn& in) {
+    if (a.at_out || a.slew_out)
+      arrive((uint32_t)in.q, sink_at(in),
+             make_float4(sink_slew(sl_d.x, in.w.y), sink_slew(sl_d.y, in.w.y), sink_slew(sl_d.z, in.w.y),
+                         sink_slew(sl_d.w, in.w.y)));
+  };
+  if (has0) sink_arrive(in0);
+  if (gs.active && gl == 0) arrive(qd, at_d, sl_d);
+  if (has1) sink_arrive(in1);
+  float acc[N_ACC] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  SinkKeep keep0{0.f, 0.f, 0.f, 0}, keep1{0.f, 0.f, 0.f, 0};
+  if (has0) keep0 = sink_sum<kGrad>(a, in0, xd, yd, acc, true, s0);
+  if (has1) keep1 = sink_sum<kGrad>(a, in1, xd, yd, acc, true, s0 + stride);
+  if (block) {
+    for (int p = s0 + 2 * stride; p < p1; p += stride) {
+      const SinkIn in = load(p);
+      sink_arrive(in);
+      require((uint32_t)in.q, sink_at(in), in.rt);
+      sink_sum<kGrad>(a, in, xd, yd, acc, true, p);
+    }
+  }
+  reduce_step<G, kRat, kGrad ? N_ACC : A_R>(acc, block, sh);
+  if (!gs.active) return;
+  const bool wire_adj = kGrad && !a.tree_adj;
+  float lbar = 0.f;
+  if (kGrad) lbar = load_adjoint(uv, acc[A_R], acc[A_F], acc[Q_R] * sl_d.z, acc[Q_F] * sl_d.w);
+  const float cl = a.c * lbar;
+  auto store = [&](const SinkKeep& k) {
+    if (a.dx) *at32(a.dx, (uint32_t)k.q) = k.gx * (cl + k.rest);
+    if (a.dy) *at32(a.dy, (uint32_t)k.q) = k.gy * (cl + k.rest);
+  };
+  if (has0) {
+    if (kRat) require((uint32_t)in0.q, sink_at(in0), in0.rt);
+    if (wire_adj) store(keep0);
+  }
+  if (gl == 0) {
+    if (kRat) require(qd, at_d, make_float4(acc[R_E0], acc[R_E1], acc[R_L0], acc[R_L1]));
+    if (kGrad && a.tree_adj) *at32(a.tree_adj, (uint32_t)p0) = make_float2(lbar, 0.f);
+    if (wire_adj && a.dx) *at32(a.dx, qd) = -(acc[X_RS] + cl * acc[X_N]);
+    if (wire_adj && a.dy) *at32(a.dy, qd) = -(acc[Y_RS] + cl * acc[Y_N]);
+  }
+  if (has1) {
+    if (kRat) require((uint32_t)in1.q, sink_at(in1), in1.rt);
+    if (wire_adj) store(keep1);
+  }
+  if (block && wire_adj && (a.dx || a.dy)) {
+    for (int p = s0 + 2 * stride; p < p1; p += stride) {
+      float scratch[N_ACC] = {};
+      store(sink_sum<kGrad>(a, load(p), xd, yd, scratch, false, p));
+    }
+  }
+}
+
+// Cells role: 16 lanes per cell, lane (k, jl) one lookup for condition k and arc jl, as the
+// forward level; cells of 5-8 inputs take a second arc per lane.  Lanes of the early
+// conditions only serve the required times.
+template <bool kGrad, bool kRat>
+__device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int gid) {
+  const int kc = gid / kCellLanes;
+  if (kc >= sl.nc) return;                     // uniform over the cell's 16 lanes
+  const int lane = gid & (kCellLanes - 1);
+  const int k = lane >> 2, jl = lane & 3, m = k >> 1, t = k & 1;
+  const int n = a.N0 + sl.c0 + kc;
+  if (!kRat && m == 0) return;                 // whole quads
+  const int4 e0 = ld(a.ell, (uint32_t)(sl.base + min(jl, sl.F - 1) * sl.nc + kc));
+  const float load = ld(a.load, (uint32_t)n);
+  uint32_t p0 = 0;
+  if (kGrad) p0 = (uint32_t)ld(a.net_off, (uint32_t)n);
+  ArcIn ain = arc_input_entry(e0, jl < sl.F, a.rec, a.wire, m, t);
+  const ArcBwd v0 = arc_from_input(a, ain, t, load);
+  ArcBwd v1{};
+  const bool wide = sl.F > kArcLanes;          // uniform over the launch
+  if (wide) {
+    ain = arc_input(a.ell, sl, kc, kArcLanes + jl, a.rec, a.wire, m, t);
+    v1 = arc_from_input(a, ain, t, load);
+  }
+  // Single words into the slots (16-byte stores after a transpose over the lanes took as long).
+  float* sw = reinterpret_cast<float*>(a.sink);
+  if (kRat) {
+    if (v0.valid) *at32(sw, 4 * rat_at((uint32_t)v0.slot) + (uint32_t)(2 * m + v0.tp)) = v0.d;
+    if (wide && v1.valid) *at32(sw, 4 * rat_at((uint32_t)v1.slot) + (uint32_t)(2 * m + v1.tp)) = v1.d;
+  }
+  if (!kGrad || m == 0) return;                // whole quads
+  float xmax = quad_reduce<kMax>(v0.xg);
+  float z = quad_reduce<kSum>(v0.valid ? fexp((v0.xg - xmax) * a.inv_gamma) : 0.f);
+  float smax = v0.valid ? v0.s : -kInf;
+  int jstar = v0.valid ? jl : STA_MAX_FANIN;
+  quad_argmax(smax, jstar);
+  if (wide) {
+    const float cm = quad_reduce<kMax>(v1.xg);
+    const float cz = quad_reduce<kSum>(v1.valid ? fexp((v1.xg - cm) * a.inv_gamma) : 0.f);
+    float s2 = v1.valid ? v1.s : -kInf;
+    int j2 = v1.valid ? kArcLanes + jl : STA_MAX_FANIN;
+    lse_merge(xmax, z, cm, cz, a.inv_gamma);
+    quad_argmax(s2, j2);
+    if (s2 > smax) {
+      smax = s2;
+      jstar = j2;
+    }
+  }
+  const float inv_z = frcp(z);
+  float lu = 0.f, lv = 0.f;
+  auto arc = [&](const ArcBwd& v, int j) {
+    const float w = v.valid ? fexp((v.xg - xmax) * a.inv_gamma) * inv_z : 0.f;
+    const bool star = v.valid && j == jstar;
+    if (v.valid) {
+      const uint32_t aj = 4 * adj_at((uint32_t)v.slot) + (uint32_t)v.tp;
+      *at32(sw, aj) = star ? -w : w;
+      *at32(sw, aj + 2u) = v.ddx;
+    }
+    if (star) *at32(sw, 4 * adj_at(p0) + (uint32_t)t) = v.dsx;
+    lu += quad_reduce<kSum>(v.valid ? w * v.ddy : 0.f);
+    lv += quad_reduce<kSum>(star ? v.dsy : 0.f);
+  };
+  arc(v0, jl);
+  if (wide) arc(v1, kArcLanes + jl);
+  if (jl == 0) {
+    *at32(sw, 4 * rat_at(p0) + (uint32_t)t) = lu;
+    *at32(sw, 4 * rat_at(p0) + 2u + (uint32_t)t) = lv;
+  }
+}
+
+// One level l >= 1: workgroups [0, n_chain) the chain role of its nets, the rest the cells of the
+// next lower level (`pre`).  The values that the chain's first loads need come first, preloaded
+// into scalar registers.
+template <bool kSnap, bool kGrad, bool kRat>
+__global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0, int e0, int e1, int e2, int e3, int w1,
+                                                     int w2, int w3, const int* __restrict__ net_off,
+                                                     const int4* __restrict__ ell, BwdArgs a0, Slots sl, Slots pre,
+                                                     LevelRanges r0, int snap_state) {
+  __shared__ float sh[kWavesPerBlock * N_ACC];
+  BwdArgs a = a0;
+  a.net_off = net_off;
+  a.ell = ell;
+  const SnapBlock sb = snap_block<kSnap>();
+  a.rec = snap_bytes<kSnap>(a.rec, (size_t)snap_state, sb.s);
+  a.wire = snap_bytes<kSnap>(a.wire, (size_t)snap_state, sb.s);
+  a.load = snap_bytes<kSnap>(a.load, (size_t)snap_state, sb.s);
+  a.sink = snap_bytes<kSnap>(a.sink, a.snap.work, sb.s);
+  if (sb.x >= n_chain) {
+    pre_cell<kGrad, kRat>(a, pre, (sb.x - n_chain) * kBlock + (int)threadIdx.x);
+    return;
+  }
+  const LevelRanges r{nh, h0, e0, e1, e2, e3, r0.e4, r0.e5, w1, w2, w3, r0.w4, r0.w5, r0.g0};
+  GroupSlot gs;
+  if (!step_slot(sb.x, r, gs)) return;
+  if (gs.block || gs.G == 64) chain_net<64, kGrad, kRat>(a, sl, gs, sh);
+  else if (gs.G == 32) chain_net<32, kGrad, kRat>(a, sl, gs, sh);
+  else if (gs.G == 16) chain_net<16, kGrad, kRat>(a, sl, gs, sh);
+  else if (gs.G == 8) chain_net<8, kGrad, kRat>(a, sl, gs, sh);
+  else chain_net<4, kGrad, kRat>(a, sl, gs, sh);
+}
+
+// Outputs of every net, after the last level.
+template <bool kGrad, bool kRat>
+__global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int* __restrict__ sched, BwdArgs a,
+                                                    int snap_state, int stream) {
+  __shared__ float sh[kWavesPerBlock * N_ACC];
+  a.rec = snap_bytes(a.rec, (size_t)snap_state);
+  a.wire = snap_bytes(a.wire, (size_t)snap_state);
+  a.sink = snap_bytes(a.sink, a.snap.work);
+  a.x = snap_elems(a.x, a.snap.pins);
+  a.y = snap_elems(a.y, a.snap.pins);
+  a.at_out = snap_elems(a.at_out, a.snap.pins);
+  a.slew_out = snap_elems(a.slew_out, a.snap.pins);
+  a.rat_out = snap_elems(a.rat_out, a.snap.pins);
+  a.slack_out = snap_elems(a.slack_out, a.snap.pins);
+  a.dx = snap_elems(a.dx, a.snap.pins);
+  a.dy = snap_elems(a.dy, a.snap.pins);
+  a.tree_adj = snap_bytes(a.tree_adj, a.snap.work);
+  GroupSlot gs;
+  if (!group_slot(range, gs)) return;
+  gs.entry = gs.active ? sched[gs.entry] : 0;
+  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat>(a, gs, stream != 0, sh);
+  else if (gs.G == 32) post_net<32, kGrad, kRat>(a, gs, stream != 0, sh);
+  else if (gs.G == 16) post_net<16, kGrad, kRat>(a, gs, stream != 0, sh);
+  else if (gs.G == 8) post_net<8, kGrad, kRat>(a, gs, stream != 0, sh);
+  else post_net<4, kGrad, kRat>(a, gs, stream != 0, sh);
+}
+
+// Seeds of the endpoints, and beside them the cells role of the deepest level.
+template <bool kGrad, bool kRat>
+__global__ __launch_bounds__(kBlock) void k_bwd_start(EpArgs ea, int n_seed, BwdArgs a, Slots pre, int snap_state) {
+  if ((int)blockIdx.x < n_seed) {
+    const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
+    if (i < ea.E) ep_seed(ep_snap(ea), i);
+    return;
+  }
+  a.rec = snap_bytes(a.rec, (size_t)snap_state);
+  a.wire = snap_bytes(a.wire, (size_t)snap_state);
+  a.load = snap_bytes(a.load, (size_t)snap_state);
+  a.sink = snap_bytes(a.sink, a.snap.work);
+  pre_cell<kGrad, kRat>(a, pre, ((int)blockIdx.x - n_seed) * kBlock + (int)threadIdx.x);
 }
 
 // One backward level's launch, with the kernel compiled for its smallest group, snapshot
@@ -2349,8 +2819,8 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level_cte(int lo, int hi, Slots 
     }
     gs_sh[0][t] = acc[A_R];
     gs_sh[1][t] = acc[A_F];
-    gs_sh[2][t] = acc[S_R];
-    gs_sh[3][t] = acc[S_F];
+    gs_sh[2][t] = acc[Q_R] * sl_d.z;
+    gs_sh[3][t] = acc[Q_F] * sl_d.w;
     gs_sh[4][t] = xmax[0];
     gs_sh[5][t] = xmax[1];
     gs_sh[6][t] = frcp(z[0]);
@@ -2377,7 +2847,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level_cte(int lo, int hi, Slots 
           const float dbar = fexp((in.atg + v.d - gs_sh[4 + tr][o]) * a.inv_gamma) * gs_sh[6 + tr][o] * gs_sh[tr][o];
           const float s_j = j == js_sh[tr][o] ? gs_sh[2 + tr][o] : 0.f;
           set_comp(adj_in, in.tp, dbar);
-          set_comp(adj_in, 2 + in.tp, fmaf(dbar, v.ddx, s_j * v.dsx));
+          set_comp(adj_in, 2 + in.tp, fmaf(dbar, v.ddx, s_j * v.dsx) * inv_slew(in.slew));
           lb = fmaf(dbar, v.ddy, fmaf(s_j, v.dsy, lb));
         }
       }
@@ -3488,6 +3958,37 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
   return STA_OK;
 }
 
+// Whether the backward levels run split by role (k_bwd_step) rather than fused (k_bwd_level).  The
+// split form saves a fixed part of a level's time (about 2 us of its dependent chain) and costs
+// memory traffic per net (its inputs' slots written twice, its sinks read twice), so the line
+// is a number of nets per level, over all snapshots.  Backward sweeps of 100k- to 2.5M-pin
+// designs in 1 to 64 snapshots, fused -> split:
+//   with required times: 788 nets a level 171 -> 117 us, 3.4k 354 -> 254, 7.4k 556 -> 540,
+//     12.6k 258 -> 258, 13.5k 587 -> 639, 27k 807 -> 1036;
+//   gradient alone (its slots are half as wide): 3.4k 326 -> 229, 7.4k 511 -> 430, 13.5k
+//     540 -> 493, 22k 948 -> 1069, 27k 712 -> 795.
+bool split_levels(const sta_graph* g, bool rat) {
+  const int64_t per_level = (int64_t)g->n_snap * g->N / std::max(1, g->L);
+  return g->ckpt_stride <= 0 && g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
+}
+
+// Whether k_bwd_out writes its outputs as streaming stores, which leave the 256 MB last-level cache
+// to the state that the next call reads again.  They pay where whole lines are written (canonical
+// order) and the outputs would fill a good part of that cache: full steps that alternate between
+// three placements, plain -> streaming: 108k pins in 8 snapshots (62 MB of outputs) 352 -> 314 us, 637k
+// pins (46 MB) 334 -> 316 us.  Outputs of more than half the cache push the state out in any case
+// and are written faster plainly (2.6M pins, 187 MB: 901 -> 883 us), and so are scattered ones
+// (414k pins with RC trees in original order: 454 -> 439 us).
+bool stream_outputs(const sta_graph* g, const int* io, const sta_bwd_out& out) {
+  const int64_t bytes = (int64_t)g->n_snap * g->P * 16 * (!!out.at + !!out.slew + !!out.rat + !!out.slack);
+  return io == nullptr && bytes <= (128ll << 20);
+}
+
+// Workgroups of the cells role over one level.
+unsigned cell_blocks(const Slots& sl) {
+  return (unsigned)(((size_t)kCellLanes * sl.nc + kBlock - 1) / kBlock);
+}
+
 sta_status launch_backward(sta_graph* g, const float* x, const float* y, const sta_fwd_out* fwd,
                            const sta_bwd_out* out, uint32_t flags, float gamma_ps, hipStream_t s) {
   if (g->lanes_kernels()) return launch_backward_si(g, x, y, fwd, out, flags, gamma_ps, s);
@@ -3513,10 +4014,12 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
     LaunchTimer t(g, s, STA_K_EP_SEED);
     k_ep_seed<<<dim3((unsigned)((n + kBlock - 1) / kBlock), g->n_snap), kBlock, 0, s>>>(ea, list, n);
   };
-  if (g->ckpt_stride <= 0)
-    ep_seed(nullptr, g->E);
-  else
+  const bool rat = out->rat || out->slack || !grad;
+  const bool split = split_levels(g, rat);
+  if (g->ckpt_stride > 0)
     ep_seed(d.ep_grp, g->ep_grp_off[1]);
+  else if (!split)
+    ep_seed(nullptr, g->E);
 
   const bool tree = !g->c_parent.empty();
   BwdArgs ba{d.net_off, d.pin_cap, d.ell, io, x, y, d.lut_grid, d.lut_coef, lut_keys(g),
@@ -3567,7 +4070,43 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
       default: bwd_launch<6, true>(grid, s, L, canon, grad); break;
     }
   };
-  if (g->ckpt_stride <= 0) {
+  if (split) {
+    const bool snap = g->n_snap > 1;
+    auto start = [&](auto kern, const Slots& pre) {
+      LaunchTimer t(g, s, STA_K_EP_SEED);
+      const unsigned n_seed = (unsigned)((g->E + kBlock - 1) / kBlock);
+      const unsigned blocks = n_seed + cell_blocks(pre);
+      if (blocks > 0) kern<<<dim3(blocks, g->n_snap), kBlock, 0, s>>>(ea, (int)n_seed, ba, pre, ss);
+    };
+    auto step = [&](auto kern, int l) {
+      const GroupRange& r = g->lvl_ranges[l];
+      const unsigned chain = range_grid(r);
+      const Slots pre = l >= 2 ? level_slots(g, l - 1) : Slots{0, 1, 0, 0};
+      const unsigned blocks = chain + cell_blocks(pre);
+      if (blocks == 0) return;
+      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+      const int* c = r.cls_off;
+      const int* w = r.wave_off;
+      const LevelRanges lr{c[kNumClasses + 1] - c[kNumClasses], c[kNumClasses], c[0], c[1], c[2], c[3], c[4], c[5],
+                           w[1], w[2], w[3], w[4], w[5], r.g0};
+      kern<<<snap ? level_grid(g, blocks) : dim3(blocks), kBlock, 0, s>>>(
+          (int)chain, lr.nh, lr.h0, lr.e0, lr.e1, lr.e2, lr.e3, lr.w1, lr.w2, lr.w3, d.net_off, d.ell, ba,
+          level_slots(g, l), pre, lr, ss);
+    };
+    auto sweep = [&](auto kstart, auto kstep, auto kout) {
+      start(kstart, level_slots(g, g->L - 1));
+      for (int l = g->L - 1; l >= 1; --l) step(kstep, l);
+      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+      kout<<<snap_grid(g, range_grid(g->all_range)), kBlock, 0, s>>>(g->all_range, d.sched_all, ba, ss,
+                                                                         stream_outputs(g, io, *out) ? 1 : 0);
+    };
+    if (!grad) snap ? sweep(k_bwd_start<false, true>, k_bwd_step<true, false, true>, k_bwd_out<false, true>)
+                    : sweep(k_bwd_start<false, true>, k_bwd_step<false, false, true>, k_bwd_out<false, true>);
+    else if (rat) snap ? sweep(k_bwd_start<true, true>, k_bwd_step<true, true, true>, k_bwd_out<true, true>)
+                       : sweep(k_bwd_start<true, true>, k_bwd_step<false, true, true>, k_bwd_out<true, true>);
+    else snap ? sweep(k_bwd_start<true, false>, k_bwd_step<true, true, false>, k_bwd_out<true, false>)
+              : sweep(k_bwd_start<true, false>, k_bwd_step<false, true, false>, k_bwd_out<true, false>);
+  } else if (g->ckpt_stride <= 0) {
     for (int l = g->L - 1; l >= 0; --l) bwd_level(l);
   } else {
     // Segments last to first: rebuild the records the forward dropped (the kept ones are
