@@ -2250,12 +2250,11 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
 }
 
 // Outputs role of one net: the net step again, for its per-pin outputs, and the Elmore adjoint.
-// The driver's part of an output follows its sinks' at once, so that streaming stores (`stream`,
-// see stream_outputs) leave L2 with whole lines: 2.6M pins in canonical order with every output
-// take 84 us with plain stores (368 MB, 4.4 TB/s), 103 us with streaming ones, and 134 us with
-// streaming ones when the driver's part comes after the reductions.
+// Bound by memory: 2.6M pins in canonical order with every output take 84 us with plain stores (368
+// MB, 4.4 TB/s; a 4 GiB copy reaches 4.8), 103 us with streaming ones, which leave L2 before a
+// line's pieces - its sinks' and its drivers' - have met there.
 template <int G, bool kGrad, bool kRat>
-__device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, bool stream, float* sh) {
+__device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, float* sh) {
   const int gl = gs.gl;
   const bool block = gs.block;
   const int n = gs.active ? gs.entry : 0;
@@ -2285,9 +2284,7 @@ __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, 
   SinkIn in1{};
   if (block) in1 = load(has1 ? s0 + stride : p0);
   auto put = [&](float4* out, uint32_t q, const float4& v) {
-    if (!out) return;
-    if (stream) store_stream(at32(out, q), v);
-    else *at32(out, q) = v;
+    if (out) *at32(out, q) = v;
   };
   auto arrive = [&](uint32_t q, const float4& at, const float4& sl) {
     put(a.at_out, q, at);
@@ -2456,7 +2453,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0
 // Outputs of every net, after the last level.
 template <bool kGrad, bool kRat>
 __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int* __restrict__ sched, BwdArgs a,
-                                                    int snap_state, int stream) {
+                                                    int snap_state) {
   __shared__ float sh[kWavesPerBlock * N_ACC];
   a.rec = snap_bytes(a.rec, (size_t)snap_state);
   a.wire = snap_bytes(a.wire, (size_t)snap_state);
@@ -2473,11 +2470,11 @@ __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int*
   GroupSlot gs;
   if (!group_slot(range, gs)) return;
   gs.entry = gs.active ? sched[gs.entry] : 0;
-  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat>(a, gs, stream != 0, sh);
-  else if (gs.G == 32) post_net<32, kGrad, kRat>(a, gs, stream != 0, sh);
-  else if (gs.G == 16) post_net<16, kGrad, kRat>(a, gs, stream != 0, sh);
-  else if (gs.G == 8) post_net<8, kGrad, kRat>(a, gs, stream != 0, sh);
-  else post_net<4, kGrad, kRat>(a, gs, stream != 0, sh);
+  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat>(a, gs, sh);
+  else if (gs.G == 32) post_net<32, kGrad, kRat>(a, gs, sh);
+  else if (gs.G == 16) post_net<16, kGrad, kRat>(a, gs, sh);
+  else if (gs.G == 8) post_net<8, kGrad, kRat>(a, gs, sh);
+  else post_net<4, kGrad, kRat>(a, gs, sh);
 }
 
 // Seeds of the endpoints, and beside them the cells role of the deepest level.
@@ -3972,18 +3969,6 @@ bool split_levels(const sta_graph* g, bool rat) {
   return g->ckpt_stride <= 0 && g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
 }
 
-// Whether k_bwd_out writes its outputs as streaming stores, which leave the 256 MB last-level cache
-// to the state that the next call reads again.  They pay where whole lines are written (canonical
-// order) and the outputs would fill a good part of that cache: full steps that alternate between
-// three placements, plain -> streaming: 108k pins in 8 snapshots (62 MB of outputs) 352 -> 314 us, 637k
-// pins (46 MB) 334 -> 316 us.  Outputs of more than half the cache push the state out in any case
-// and are written faster plainly (2.6M pins, 187 MB: 901 -> 883 us), and so are scattered ones
-// (414k pins with RC trees in original order: 454 -> 439 us).
-bool stream_outputs(const sta_graph* g, const int* io, const sta_bwd_out& out) {
-  const int64_t bytes = (int64_t)g->n_snap * g->P * 16 * (!!out.at + !!out.slew + !!out.rat + !!out.slack);
-  return io == nullptr && bytes <= (128ll << 20);
-}
-
 // Workgroups of the cells role over one level.
 unsigned cell_blocks(const Slots& sl) {
   return (unsigned)(((size_t)kCellLanes * sl.nc + kBlock - 1) / kBlock);
@@ -4097,8 +4082,7 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
       start(kstart, level_slots(g, g->L - 1));
       for (int l = g->L - 1; l >= 1; --l) step(kstep, l);
       LaunchTimer t(g, s, STA_K_BWD_LEVEL);
-      kout<<<snap_grid(g, range_grid(g->all_range)), kBlock, 0, s>>>(g->all_range, d.sched_all, ba, ss,
-                                                                         stream_outputs(g, io, *out) ? 1 : 0);
+      kout<<<snap_grid(g, range_grid(g->all_range)), kBlock, 0, s>>>(g->all_range, d.sched_all, ba, ss);
     };
     if (!grad) snap ? sweep(k_bwd_start<false, true>, k_bwd_step<true, false, true>, k_bwd_out<false, true>)
                     : sweep(k_bwd_start<false, true>, k_bwd_step<false, false, true>, k_bwd_out<false, true>);
