@@ -988,6 +988,10 @@ sta_status sta_graph_upload(sta_graph* g) {
   d.device = dev;
   std::vector<float4> grid, coef;
   build_lut_coefficients(g, grid, coef);
+  const LutKeys keys = lut_keys(g);            // grid, breakpoints and coefficients in one array
+  grid.resize(kLutCoefAt, make_float4(0.f, 0.f, 0.f, 0.f));
+  std::memcpy(&grid[kLutKeysAt], &keys, sizeof(keys));
+  grid.insert(grid.end(), coef.begin(), coef.end());
 
   auto up = [&](auto*& dst, const auto& src) -> sta_status {
     using T = std::remove_reference_t<decltype(*dst)>;
@@ -1015,10 +1019,11 @@ sta_status sta_graph_upload(sta_graph* g) {
       (!g->c_parent.empty() && ((s = up(d.parent, g->c_parent)) || (s = up(d.tree_order, g->c_tree_order)) ||
                                 (s = up(d.tree_node, g->c_tree_node)) || (s = up(d.tree_blk_net, g->tree_blk_net)) ||
                                 (s = up(d.tree_blk_depth, g->tree_blk_depth)) || (s = up(d.tree_big, g->tree_big)))) ||
-      (s = up(d.lut_grid, grid)) || (s = up(d.lut_coef, coef))) {
+      (s = up(d.lut_grid, grid))) {
     free_device(g);
     return s;
   }
+  d.lut_coef = d.lut_grid + kLutCoefAt;
   g->uploaded = true;
   return STA_OK;
 }

@@ -16,6 +16,8 @@ constexpr int kBlock = 256;          // threads per workgroup (4 wave64s)
 constexpr int kNumClasses = 5;       // wave lane groups of 4, 8, 16, 32, 64 lanes per net
 constexpr int kHeavy = kNumClasses;  // class of nets served by a whole workgroup
 constexpr int kLutCells = (STA_LUT_N - 1) * (STA_LUT_N - 1);
+constexpr int kLutKeysAt = kLutCells;      // in the tables' device array: the breakpoints (LutKeys,
+constexpr int kLutCoefAt = kLutCells + 3;  // three float4) follow the grid, then the coefficients
 constexpr int kFlatG0Default = 2;    // flat kernels (RC, outputs): smallest group 4 lanes
 constexpr int kSweepG0Default = 2;   // level kernels: smallest backward group 4 lanes (one per condition)
 constexpr int kTreeChunk = 1024;     // RC trees: pins of whole nets swept by one workgroup in LDS
@@ -96,8 +98,9 @@ struct DeviceGraph {
   int* tree_blk_net = nullptr;    // RC trees only: chunk net ranges
   int* tree_blk_depth = nullptr;  // RC trees only: deepest depth of each chunk
   int* tree_big = nullptr;        // RC trees only: nets over the chunk size
-  float4* lut_grid = nullptr;  // [36] {x_i, 1/(x_i+1 - x_i), y_j, 1/(y_j+1 - y_j)}
-  float4* lut_coef = nullptr;  // [n_arcs * 2 * 36 * 2] bilinear coefficients {a, b, c, d}
+  float4* lut_grid = nullptr;  // [36] {x_i, 1/(x_i+1 - x_i), y_j, 1/(y_j+1 - y_j)}, then LutKeys
+  float4* lut_coef = nullptr;  // [n_arcs * 2 * 36 * 2] bilinear coefficients {a, b, c, d}; in one
+                               // array with the grid, from kLutCoefAt
   int* sink_base = nullptr;    // [N] checkpointing (stars): first slot of each net's sinks
   int* ep_sslot = nullptr;     // [E] checkpointing (stars): workspace slot of each endpoint
   int* ep_grp = nullptr;       // [E] checkpointing: endpoint indices grouped by segment

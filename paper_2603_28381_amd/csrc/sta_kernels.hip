@@ -1105,14 +1105,39 @@ __device__ __forceinline__ ArcIn arc_input(const int4* __restrict__ ell, const S
 
 // ---------------------------------------------------------------------------- forward level
 // Arguments of a forward level that the first loads do not need.
+// A launch whose arguments fit 96 bytes costs the host 2.75 us instead of 3.15 (measured on empty
+// kernels of 16 to 520 bytes: flat up to 96, flat from 192), and small designs are bound by
+// it; hence one pointer for the tables, and the breakpoints through scalar loads.
 struct FwdArgs {
   const float2* __restrict__ wire;
-  const float4* __restrict__ grid;
-  const float4* __restrict__ coef;
-  LutKeys keys;
-  float gamma, inv_gamma;
-  int smooth;
+  const float4* __restrict__ lut;   // grid, breakpoints, coefficients (see kLutKeysAt)
+  float gamma, inv_gamma;           // inv_gamma 0: no smoothing
+  int next_F, next_nc;              // the next level's input slots, which follow this level's
+                                    // (next_nc 0: nothing to prefetch)
 };
+
+// The tables' device array: grid cells, breakpoints, coefficients.
+__device__ __forceinline__ LutKeys lut_keys_at(const float4* lut) {
+  const float4 a = ld_const(lut, kLutKeysAt), b = ld_const(lut, kLutKeysAt + 1), c = ld_const(lut, kLutKeysAt + 2);
+  return LutKeys{{a.x, a.y, a.z, a.w, b.x}, {b.y, b.z, b.w, c.x, c.y}};
+}
+
+// A level's first loads - its cells' input slots and root loads - depend on no other level, and
+// come from memory (430 ns) unless something has just read them.  Extra workgroups of the
+// level before read them into the L2 that the level will look in: workgroups go to the 8 XCDs
+// round-robin, so the prefetching ones start at a multiple of 8, and the b-th takes the cells
+// of the next launch's b-th.  Sweeps of 63k and 841k pins 199 -> 194 and 253 -> 242 us (0.18 us a
+// level); started at another offset (another XCD's L2) 255 us.
+__host__ __device__ inline int level_blocks(int cells, int lanes) { return (cells * lanes + kBlock - 1) / kBlock; }
+__host__ __device__ inline int prefetch_block(int cells) { return (level_blocks(cells, kCellLanes) + 7) & ~7; }
+__device__ __forceinline__ void fwd_prefetch(const int4* __restrict__ ell, const float* __restrict__ loads, int base,
+                                             int F, int nc, int n0, int b) {
+  const int kc = b * (kBlock / kCellLanes) + (int)(threadIdx.x >> 2), j = (int)(threadIdx.x & 3);
+  if (threadIdx.x >= 4 * (kBlock / kCellLanes) || kc >= nc) return;
+  const int4 e = ld(ell, (uint32_t)(base + min(j, F - 1) * nc + kc));
+  const float load = ld(loads, (uint32_t)(n0 + kc));
+  asm volatile("" ::"v"(e.x), "v"(load));      // the loads stay, their values are not needed
+}
 
 // One level of forward propagation (Sec. 3.1.2).  16 lanes per cell: lane (k, j) looks up
 // arc j for condition k = 2*mode + transition; the 4 arc lanes of a condition then merge
@@ -1135,7 +1160,16 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level(int nc, int n0, int base, 
   a.wire = snap_bytes<kSnap>(a.wire, (size_t)snap_state, sb.s);
   const int gid = sb.x * kBlock + (int)threadIdx.x;
   const int kc = gid / kCellLanes;
+  if (!kSnap && a.next_nc > 0) {
+    const int b = sb.x - prefetch_block(nc);
+    if (b >= 0) {
+      fwd_prefetch(ell, loads, base + F * nc, a.next_F, a.next_nc, n0 + nc, b);
+      return;
+    }
+  }
   if (kc >= sl.nc) return;                     // uniform over the cell's 16 lanes
+  const LutKeys keys = lut_keys_at(a.lut);
+  const float4* coef = a.lut + kLutCoefAt;
   const int lane = gid & (kCellLanes - 1);
   const int k = lane >> 2, jl = lane & 3, m = k >> 1, t = k & 1;
   const int n = n0 + kc;
@@ -1145,13 +1179,14 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level(int nc, int n0, int base, 
   const float load = ld(loads, (uint32_t)n);
   const int slot = loc ? ld(loc, (uint32_t)n) : n;
   if (slot < min_slot) return;                 // kept record, not recomputed
+  const bool smooth = a.inv_gamma > 0.f;
   float best_at = m ? -kInf : kInf;
   float best_sl = best_at;
   float lm = -kInf, ls = 0.f;
   for (int j0 = 0; j0 < sl.F; j0 += kArcLanes) {
     const ArcIn in = j0 == 0 ? arc_input_entry(e0, jl < sl.F, rec, a.wire, m, t)
                              : arc_input(ell, sl, kc, j0 + jl, rec, a.wire, m, t);
-    const LutVal v = lut_eval<false>(a.grid, a.coef, a.keys, in.arc, t, in.slew, load);
+    const LutVal v = lut_eval<false>(a.lut, coef, keys, in.arc, t, in.slew, load);
     float cand = m ? -kInf : kInf, s = cand, g = -kInf;
     if (in.valid) {
       cand = in.at + v.d;
@@ -1161,7 +1196,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level(int nc, int n0, int base, 
     if (m) {
       best_at = fmaxf(best_at, quad_reduce<kMax>(cand));
       best_sl = fmaxf(best_sl, quad_reduce<kMax>(s));
-      if (a.smooth) {
+      if (smooth) {
         const float gm = quad_reduce<kMax>(g);
         const float gs = quad_reduce<kSum>(in.valid ? fexp((g - gm) * a.inv_gamma) : 0.f);
         lse_merge(lm, ls, gm, gs, a.inv_gamma);
@@ -1172,7 +1207,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level(int nc, int n0, int base, 
     }
   }
   if (jl == 0) {
-    const float ag = m ? (a.smooth ? fmaf(a.gamma, flog(ls), lm) : __builtin_nanf("")) : 0.f;
+    const float ag = m ? (smooth ? fmaf(a.gamma, flog(ls), lm) : __builtin_nanf("")) : 0.f;
     *at32(rec, (uint32_t)(kRecChunks * slot + k)) = make_float4(best_at, best_sl, ag, 0.f);
   }
 }
@@ -1211,6 +1246,8 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_narrow(int nc, int n0, int
   const int gid = sb.x * kBlock + (int)threadIdx.x;
   const int kc = gid / kLanes;
   if (kc >= sl.nc) return;                     // uniform over the cell's lanes
+  const LutKeys keys = lut_keys_at(a.lut);
+  const float4* coef = a.lut + kLutCoefAt;
   const int lane = gid & (kLanes - 1);
   const int k = lane / L, jl = lane % L, m = k >> 1, t = k & 1;
   const int n = n0 + kc;
@@ -1223,6 +1260,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_narrow(int nc, int n0, int
   const float load = ld(loads, (uint32_t)n);
   const int slot = loc ? ld(loc, (uint32_t)n) : n;
   if (slot < min_slot) return;                 // kept record, not recomputed
+  const bool smooth = a.inv_gamma > 0.f;
   float best_at = m ? -kInf : kInf;
   float best_sl = best_at;
   float lm = -kInf, ls = 0.f;
@@ -1236,7 +1274,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_narrow(int nc, int n0, int
     }
     LutVal v[kArcs];
 #pragma unroll
-    for (int i = 0; i < kArcs; ++i) v[i] = lut_eval<false>(a.grid, a.coef, a.keys, in[i].arc, t, in[i].slew, load);
+    for (int i = 0; i < kArcs; ++i) v[i] = lut_eval<false>(a.lut, coef, keys, in[i].arc, t, in[i].slew, load);
     const float neutral = m ? -kInf : kInf;
     float g[kArcs];
     float cm = neutral, sm = neutral, gm = -kInf;
@@ -1257,7 +1295,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_narrow(int nc, int n0, int
     if (m) {
       best_at = fmaxf(best_at, pair_reduce_max<L>(cm));
       best_sl = fmaxf(best_sl, pair_reduce_max<L>(sm));
-      if (a.smooth) {
+      if (smooth) {
         gm = pair_reduce_max<L>(gm);
         float gs = 0.f;
 #pragma unroll
@@ -1270,7 +1308,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_narrow(int nc, int n0, int
     }
   }
   if (jl == 0) {
-    const float ag = m ? (a.smooth ? fmaf(a.gamma, flog(ls), lm) : __builtin_nanf("")) : 0.f;
+    const float ag = m ? (smooth ? fmaf(a.gamma, flog(ls), lm) : __builtin_nanf("")) : 0.f;
     *at32(rec, (uint32_t)(kRecChunks * slot + k)) = make_float4(best_at, best_sl, ag, 0.f);
   }
 }
@@ -2630,6 +2668,9 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_cte(int nc, int n0, int ba
                                                           const int4* __restrict__ ell,
                                                           const float* __restrict__ loads,
                                                           float4* __restrict__ rec, FwdArgs a) {
+  const LutKeys keys = lut_keys_at(a.lut);
+  const float4* coef = a.lut + kLutCoefAt;
+  const bool smooth = a.inv_gamma > 0.f;
   __shared__ int pre[kBlock];
   __shared__ int total_sh;
   __shared__ float load_sh[kBlock];
@@ -2661,7 +2702,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_cte(int nc, int n0, int ba
       for (int k = 0; k < 4; ++k) {
         const int m = k >> 1, tr = k & 1;
         const ArcIn in = arc_input_entry(e, true, rec, a.wire, m, tr);
-        const LutVal v = lut_eval<false>(a.grid, a.coef, a.keys, in.arc, tr, in.slew, load);
+        const LutVal v = lut_eval<false>(a.lut, coef, keys, in.arc, tr, in.slew, load);
         part[k][task - c0] = in.at + v.d;
         part[4 + k][task - c0] = v.s;
         if (m) part[8 + tr][task - c0] = in.atg + v.d;
@@ -2681,7 +2722,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_cte(int nc, int n0, int ba
           bsl[k] = fminf(bsl[k], part[4 + k][q]);
         }
       }
-      if (a.smooth) {
+      if (smooth) {
         lse_merge(lm[0], ls[0], part[8][q], 1.f, a.inv_gamma);
         lse_merge(lm[1], ls[1], part[9][q], 1.f, a.inv_gamma);
       }
@@ -2692,7 +2733,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level_cte(int nc, int n0, int ba
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int m = k >> 1, tr = k & 1;
-    const float ag = m ? (a.smooth ? fmaf(a.gamma, flog(ls[tr]), lm[tr]) : __builtin_nanf("")) : 0.f;
+    const float ag = m ? (smooth ? fmaf(a.gamma, flog(ls[tr]), lm[tr]) : __builtin_nanf("")) : 0.f;
     rec[kRecChunks * (size_t)n + k] = make_float4(bat[k], bsl[k], ag, 0.f);
   }
 }
@@ -3688,10 +3729,14 @@ void fwd_narrow_launch(dim3 grid, bool snap, hipStream_t s, const Slots& sl, int
                                                          fa);
 }
 
-void fwd_level_launch(const sta_graph* g, hipStream_t s, const Slots& sl, int min_slot, int ss, const int4* ell,
-                      const float* load, const int* loc, float4* rec, const FwdArgs& fa) {
+// Levels of more cells gain nothing from the prefetch (2.6M pins, 7.3k cells: 899 -> 903 us).
+constexpr int kPrefetchCells = 5000;
+
+// `next`: the level launched after this one (no cells: none).
+void fwd_level_launch(const sta_graph* g, hipStream_t s, const Slots& sl, const Slots& next, int min_slot, int ss,
+                      const int4* ell, const float* load, const int* loc, float4* rec, const FwdArgs& fa) {
   const int lanes = g->sched_cfg.fwd_cell_lanes;
-  const unsigned blocks = (unsigned)(((size_t)lanes * sl.nc + kBlock - 1) / kBlock);
+  const unsigned blocks = (unsigned)level_blocks(sl.nc, lanes);
   if (blocks == 0) return;
   const int n0 = g->N0 + sl.c0;
   const bool snap = g->n_snap > 1;
@@ -3703,7 +3748,14 @@ void fwd_level_launch(const sta_graph* g, hipStream_t s, const Slots& sl, int mi
   } else if (snap) {
     k_fwd_level<true><<<grid, kBlock, 0, s>>>(sl.nc, n0, sl.base, sl.F, min_slot, ss, ell, load, loc, rec, fa);
   } else {
-    k_fwd_level<false><<<grid, kBlock, 0, s>>>(sl.nc, n0, sl.base, sl.F, min_slot, ss, ell, load, loc, rec, fa);
+    FwdArgs f = fa;
+    dim3 one = grid;
+    if (next.nc > 0 && next.nc <= kPrefetchCells) {
+      f.next_F = next.F;
+      f.next_nc = next.nc;
+      one.x = (unsigned)(prefetch_block(sl.nc) + level_blocks(next.nc, kCellLanes));
+    }
+    k_fwd_level<false><<<one, kBlock, 0, s>>>(sl.nc, n0, sl.base, sl.F, min_slot, ss, ell, load, loc, rec, f);
   }
 }
 
@@ -3907,8 +3959,7 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
     k_ep_values<<<dim3((unsigned)((n + kBlock - 1) / kBlock), g->n_snap), kBlock, 0, s>>>(ea, d.ep_grp + lo, n);
   };
   if (ckpt) ep_values(0);
-  const FwdArgs fa{wire, d.lut_grid, d.lut_coef, lut_keys(g), gamma_ps, smooth ? 1.0f / gamma_ps : 0.f,
-                   smooth ? 1 : 0};
+  const FwdArgs fa{wire, d.lut_grid, gamma_ps, smooth ? 1.0f / gamma_ps : 0.f, 1, 0};
   const bool cte = g->sched_cfg.level_scheme == STA_LEVEL_CTE;
   for (int l = 1; l < g->L; ++l) {
     if (ckpt) {                                // a segment starts: its nets' RC pass
@@ -3929,7 +3980,8 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
       k_fwd_level_cte<<<(unsigned)((sl.nc + kCteItems - 1) / kCteItems), kBlock, 0, s>>>(
           sl.nc, g->N0 + sl.c0, sl.base, sl.F, d.ell, load, rec, fa);
     else
-      fwd_level_launch(g, s, sl, 0, (int)sn.state, d.ell, load, d.rec_loc, rec, fa);
+      fwd_level_launch(g, s, sl, l + 1 < g->L ? level_slots(g, l + 1) : Slots{0, 1, 0, 0}, 0, (int)sn.state, d.ell,
+                       load, d.rec_loc, rec, fa);
   }
 
   if (ckpt && g->seg_lo.size() > 1) ep_values((int)g->seg_lo.size() - 1);   // the last segment's
@@ -4096,8 +4148,7 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
     // Segments last to first: rebuild the records the forward dropped (the kept ones are
     // left alone), then that segment's backward levels.  The recomputation needs the
     // smoothed arrival only where the gradient reads it.
-    const FwdArgs fa{wire, d.lut_grid, d.lut_coef, lut_keys(g), gamma_ps, grad ? 1.0f / gamma_ps : 0.f,
-                     grad ? 1 : 0};
+    const FwdArgs fa{wire, d.lut_grid, gamma_ps, grad ? 1.0f / gamma_ps : 0.f, 1, 0};
     const RcArgs ra{d.net_off, d.pin_cap, x, y, io, d.sched_all, g->all_range, wire, load, rec, g->N0, g->N,
                     g->cons.r_per_um, g->cons.c_per_um, g->cons.pi_at, g->cons.pi_slew, snap_of(g), nullptr,
                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, d.sink_base};
@@ -4111,7 +4162,8 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
         const Slots sl = level_slots(g, l);
         if (sl.nc == 0) continue;
         LaunchTimer t(g, s, STA_K_RECOMPUTE);
-        fwd_level_launch(g, s, sl, g->n_kept, ss, d.ell, load, d.rec_loc, rec, fa);
+        fwd_level_launch(g, s, sl, l + 1 < hi ? level_slots(g, l + 1) : Slots{0, 1, 0, 0}, g->n_kept, ss, d.ell, load,
+                         d.rec_loc, rec, fa);
       }
       ep_seed(d.ep_grp + g->ep_grp_off[(size_t)j + 1], g->ep_grp_off[(size_t)j + 2] - g->ep_grp_off[(size_t)j + 1]);
       for (int l = hi - 1; l >= lo; --l) bwd_level(l);
