@@ -1626,7 +1626,7 @@ struct BwdArgs {
 // Accumulators of the net step (reduced over the group).
 // The driver's slew adjoint is its slew times Q: d slew(sink) / d slew(driver) is their ratio, and
 // the sinks hold their slew adjoint already divided by their own slew.
-enum { R_E0, R_E1, R_L0, R_L1, A_R, A_F, Q_R, Q_F, X_RS, X_N, Y_RS, Y_N, N_ACC, S_R = Q_R, S_F = Q_F };
+enum { R_E0, R_E1, R_L0, R_L1, A_R, A_F, Q_R, Q_F, X_RS, X_N, Y_RS, Y_N, N_ACC };
 
 struct SinkKeep {     // what phase 3 needs of a sink, kept in registers
   float gx, gy, rest;
@@ -3001,7 +3001,7 @@ __device__ __forceinline__ float plane_pick(const float4& v, int m, bool same, i
 // workgroup per net and block of up to 64 snapshots) and min(sl2, 3) beyond (a workgroup per
 // 8 snapshots).
 // Workgroup hb of a class serves net hb / nch of the class and snapshot chunk hb % nch.
-__device__ __forceinline__ int chunks_of(int S, int hl2) { return (S + (1 << hl2) - 1) >> hl2; }
+__host__ __device__ inline int chunks_of(int S, int hl2) { return (S + (1 << hl2) - 1) >> hl2; }
 
 // Snapshots a backward heavy workgroup of kb threads takes (log2): each snapshot keeps at least
 // 8 threads for nets of up to kSiHuge sinks (64 snapshots at kb = 512) and at least 64 beyond
@@ -3014,11 +3014,6 @@ __host__ __device__ inline int si_bwd_hl2(int sl2, int kb, bool huge) {
   const int l2 = si_log2(kb) - (huge ? kSiHugeTpsL2 : kSiHeavyTpsL2);
   return sl2 < l2 ? sl2 : l2;
 }
-constexpr int kSiCacheHeavy = 16;    // sinks a heavy workgroup's thread keeps on chip (all of a
-                                     // net of up to 128 sinks at 8 threads per snapshot)
-constexpr int kSiRows = 29;          // LDS rows of kB floats in the backward: N_ACC reductions
-                                     // and lbar, then the sink cache (kSiHeavy rows outside
-                                     // heavy workgroups)
 __device__ __forceinline__ SiLane si_heavy_lane(int hl2, int S, int chunk) {
   const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
   SiLane r;
@@ -3432,13 +3427,15 @@ __global__ __launch_bounds__(kBlock) void k_expand_si(ExpandSiArgs a) {
 }
 
 // ---------------------------------------------------------------- backward level, snapshot lanes
+// The level kernel only carries what the next level waits for: the net step's reductions and
+// the cell step.  Per-pin outputs and the Elmore adjoint follow in one pass over all nets
+// (k_bwd_out_si), from the same sinks and each net's load adjoint, which the level leaves in the
+// slot of the driver pin (no sink's).  Fused in the level they held 117 registers and 30 KB of LDS a
+// workgroup, so that a level's waves did not fit the chip at once, and streamed their outputs
+// at the level's pace.
 struct BwdSiArgs {
   const int* __restrict__ net_off;
-  const float* __restrict__ pin_cap;
   const int4* __restrict__ ell;
-  const int* __restrict__ io_perm;
-  const float* __restrict__ x;
-  const float* __restrict__ y;
   const float4* __restrict__ grid;
   const float4* __restrict__ coef;
   LutKeys keys;
@@ -3446,80 +3443,30 @@ struct BwdSiArgs {
   const float2* __restrict__ wire;
   const float* __restrict__ load;
   float4* __restrict__ sink;   // a net's sinks are read, other nets' input pins written
-  float4* __restrict__ at_out;
-  float4* __restrict__ slew_out;
-  float4* __restrict__ rat_out;
-  float4* __restrict__ slack_out;
-  float* __restrict__ dx;
-  float* __restrict__ dy;
   int N0, S, sl2;
-  float r, c, inv_gamma;
+  float inv_gamma;
 };
 
-struct SinkSi {
-  float gx, gy, rest;
-  uint32_t o;   // the pin's element in the caller's per-pin arrays
-};
+// The load adjoint of the net driven by pin p0, in the rows of that pin's workspace slot.
+__device__ __forceinline__ uint32_t lbar_at(int p0, uint32_t S, int s) { return 8u * (uint32_t)p0 * S + (uint32_t)s; }
 
-// Sink p of snapshot s in the net step (as sink_step): per-pin outputs when `write`, and its
-// contribution to the driver's reductions.
-template <bool kGrad>
-__device__ __forceinline__ SinkSi sink_si(const BwdSiArgs& a, int p, int s, const float4& at_d, const float4& sl_d,
-                                          float xd, float yd, float (&acc)[N_ACC], bool write) {
-  const uint32_t S = (uint32_t)a.S;
-  const float4 rt = ld(a.sink, si_at(2 * p, S, s));
-  const float2 w = ld(a.wire, si_at(p, S, s));
-  const uint32_t o = si_at(a.io_perm ? ld(a.io_perm, (uint32_t)p) : p, S, s);
-  const float4 ats = make_float4(at_d.x + w.x, at_d.y + w.x, at_d.z + w.x, at_d.w + w.x);
-  const float4 sls = make_float4(sink_slew(sl_d.x, w.y), sink_slew(sl_d.y, w.y), sink_slew(sl_d.z, w.y),
-                                 sink_slew(sl_d.w, w.y));
-  if (write) {
-    if (a.at_out) store_stream(at32(a.at_out, o), ats);
-    if (a.slew_out) store_stream(at32(a.slew_out, o), sls);
-    if (a.rat_out) store_stream(at32(a.rat_out, o), rt);
-    if (a.slack_out)
-      store_stream(at32(a.slack_out, o), make_float4(ats.x - rt.x, ats.y - rt.y, rt.z - ats.z, rt.w - ats.w));
-  }
-  acc[R_E0] = fmaxf(acc[R_E0], rt.x - w.x);
-  acc[R_E1] = fmaxf(acc[R_E1], rt.y - w.x);
-  acc[R_L0] = fminf(acc[R_L0], rt.z - w.x);
-  acc[R_L1] = fminf(acc[R_L1], rt.w - w.x);
-  SinkSi k{0.f, 0.f, 0.f, o};
-  if (kGrad) {
-    const float4 aj = ld(a.sink, si_at(2 * p + 1, S, s));
-    const float xs = ld(a.x, o), ys = ld(a.y, o), cp = ld(a.pin_cap, (uint32_t)p);
-    const float q0 = sls.z > 0.f ? aj.z * frcp(sls.z) : 0.f;
-    const float q1 = sls.w > 0.f ? aj.w * frcp(sls.w) : 0.f;
-    acc[A_R] += aj.x;
-    acc[A_F] += aj.y;
-    acc[S_R] += q0 * sl_d.z;
-    acc[S_F] += q1 * sl_d.w;
-    const float dbar = aj.x + aj.y;
-    const float ibar = (q0 + q1) * w.y;
-    const float len = fabsf(xs - xd) + fabsf(ys - yd);
-    k.rest = (dbar + ibar) * (1e-3f * a.r * fmaf(a.c, len, cp));
-    k.gx = sgnf(xs - xd);
-    k.gy = sgnf(ys - yd);
-    acc[X_RS] += k.gx * k.rest;
-    acc[X_N] += k.gx;
-    acc[Y_RS] += k.gy * k.rest;
-    acc[Y_N] += k.gy;
-  }
-  return k;
+// Late slews of record r: the second half of its slew row's element.
+__device__ __forceinline__ float2 rec_late_slew_si(const float4* __restrict__ rec, int r, uint32_t S, int s) {
+  return ld(reinterpret_cast<const float2*>(rec), 2u * si_at(kRecChunks * r + 1, S, s) + 1u);
 }
 
-// Cell step of cell kc in snapshot s, one pass over its arcs: the inputs' required times, and
+// Cell step of cell kc in snapshot s, one pass over its arcs: the inputs' required times (kRat), and
 // with the gradient the split of the driver's adjoint over the arcs and the slew and load
 // adjoints, which it returns.  The softmax weight of an arc is exp((x_j - ATg) / gamma), with
 // ATg the driver's smoothed arrival that the forward kept (its maximum plus gamma times the log
 // of its sum, Eq. 4); the slew adjoint goes to the first arc whose output slew equals the
 // driver's kept worst slew (the forward took that maximum over the same lookups, bit for bit).
-template <bool kGrad>
+template <bool kGrad, bool kRat>
 __device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, const Slots& sl, int kc, int s, float load,
                                               const float (&acc)[N_ACC], float2 atg, float2 worst) {
   const uint32_t S = (uint32_t)a.S;
   const float rat_o[4] = {acc[R_E0], acc[R_E1], acc[R_L0], acc[R_L1]};
-  const float abar[2] = {acc[A_R], acc[A_F]}, sbar[2] = {acc[S_R], acc[S_F]};
+  const float abar[2] = {acc[A_R], acc[A_F]}, sbar[2] = {acc[Q_R] * worst.x, acc[Q_F] * worst.y};
   const float ag[2] = {atg.x, atg.y}, smax[2] = {worst.x, worst.y};
   bool open[2] = {true, true};    // the worst-slew arc of the transition not met yet
   float lb[2] = {0.f, 0.f};
@@ -3529,16 +3476,23 @@ __device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, const Slots& s
     if (e.x < 0) continue;
     const bool same = ell_positive(e);
     const float2 w = ld(a.wire, si_at(e.y, S, s));
-    const float4 isl = rec_sl_si(a.rec, e.x, S, s);             // the input's slews
+    float4 isl = make_float4(0.f, 0.f, 0.f, 0.f);               // the input's slews
+    if (kRat) {
+      isl = rec_sl_si(a.rec, e.x, S, s);
+    } else {
+      const float2 late = rec_late_slew_si(a.rec, e.x, S, s);
+      isl.z = late.x;
+      isl.w = late.y;
+    }
     const float2 iag = kGrad ? rec_ag_si(a.rec, e.x, S, s) : make_float2(0.f, 0.f);
     float4 rat_in = make_float4(0.f, 0.f, 0.f, 0.f), adj_in = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = kRat ? 0 : 2; k < 4; ++k) {
       const int m = k >> 1, t = k & 1;
       const int tp = same ? t : 1 - t;
-      const LutVal v =
-          lut_eval_si<kGrad>(a.grid, a.coef, a.keys, ell_arc(e), t, sink_slew(plane_pick(isl, m, same, t), w.y), load);
-      set_comp(rat_in, 2 * m + tp, rat_o[k] - v.d);
+      const float slew = sink_slew(plane_pick(isl, m, same, t), w.y);
+      const LutVal v = lut_eval_si<kGrad>(a.grid, a.coef, a.keys, ell_arc(e), t, slew, load);
+      if (kRat) set_comp(rat_in, 2 * m + tp, rat_o[k] - v.d);
       if (kGrad && m == 1) {
         const float xg = (((same == (t == 0)) ? iag.x : iag.y) + w.x) + v.d;
         const float dbar = fexp((xg - ag[t]) * a.inv_gamma) * abar[t];
@@ -3546,130 +3500,81 @@ __device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, const Slots& s
         open[t] = open[t] && !star;
         const float s_j = star ? sbar[t] : 0.f;
         set_comp(adj_in, tp, dbar);
-        set_comp(adj_in, 2 + tp, fmaf(dbar, v.ddx, s_j * v.dsx));
+        set_comp(adj_in, 2 + tp, fmaf(dbar, v.ddx, s_j * v.dsx) * inv_slew(slew));
         lb[t] = fmaf(dbar, v.ddy, fmaf(s_j, v.dsy, lb[t]));
       }
     }
-    *at32(a.sink, si_at(2 * e.y, S, s)) = rat_in;
+    if (kRat) *at32(a.sink, si_at(2 * e.y, S, s)) = rat_in;
     if (kGrad) *at32(a.sink, si_at(2 * e.y + 1, S, s)) = adj_in;
   }
   return lb[0] + lb[1];
 }
 
-// Backward work of net n for the lane's snapshot (the three phases of bwd_net).  In a heavy
-// workgroup (kHeavy) of kB threads the kB >> hl2 threads of a snapshot split the sinks and their
-// reductions meet in LDS in thread order; the first thread of each snapshot then runs the
-// cell step.
-template <bool kGrad, bool kHeavy, int kB>
+// Net and cell step of net n for the lane's snapshot.  In a heavy workgroup (kHeavy) of kB threads
+// the kB >> hl2 threads of a snapshot split the sinks and their reductions meet in LDS by a fixed
+// tree; the first thread of each snapshot then runs the cell step.
+template <bool kGrad, bool kRat, bool kHeavy, int kB>
 __device__ __forceinline__ void bwd_net_si(const BwdSiArgs& a, const Slots& sl, int n, const SiLane& ln, int hl2,
                                            float* sh) {
+  constexpr int i0 = kRat ? 0 : (int)A_R, i1 = kGrad ? (int)X_RS : (int)A_R;   // reductions in use
   const uint32_t S = (uint32_t)a.S;
   const int s = ln.on ? ln.s : 0;
   const int p0 = ld(a.net_off, (uint32_t)n), p1 = ld(a.net_off, (uint32_t)n + 1u);
-  const float4 at_d = rec_at_si(a.rec, n, S, s);
-  const float4 sl_d = rec_sl_si(a.rec, n, S, s);
+  const float2 sl_d = kGrad ? rec_late_slew_si(a.rec, n, S, s) : make_float2(0.f, 0.f);
   const float2 ag_d = kGrad ? rec_ag_si(a.rec, n, S, s) : make_float2(0.f, 0.f);
-  float xd = 0.f, yd = 0.f;
-  if (kGrad && ln.on) driver_xy_si(a.x, a.y, a.io_perm, p0, S, s, xd, yd);
   float acc[N_ACC] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const int lanes = 1 << hl2;                   // heavy workgroups: snapshots per workgroup
   const int first = kHeavy ? ln.item : 0;
   const int stride = kHeavy ? kB / lanes : 1;
-  // What the Elmore adjoint needs of a thread's first sinks stays on chip: the sink's share in
-  // this thread's column of the LDS array (rows from `crow`), the signs of its x and y offsets
-  // as 2-bit codes (sign + 1) in two registers.  The adjoint pass then reads none of those
-  // sinks again.  A lane outside heavy workgroups keeps kSiHeavy sinks (all of a net of that
-  // class), a heavy workgroup's thread kSiCacheHeavy.
-  constexpr int kCache = kHeavy ? kSiCacheHeavy : kSiHeavy;
-  constexpr int crow = kHeavy ? N_ACC + 1 : 0;
-  static_assert(crow + kCache <= kSiRows && 2 * kCache <= 32, "sink cache must fit the LDS array and codes");
-  uint32_t gxs = 0, gys = 0;
   if (ln.on) {
-    int i = 0;
 #pragma unroll 4
-    for (int p = p0 + 1 + first; p < p1; p += stride, ++i) {
-      const SinkSi k = sink_si<kGrad>(a, p, s, at_d, sl_d, xd, yd, acc, true);
-      if (kGrad && i < kCache) {
-        sh[(crow + i) * kB + threadIdx.x] = k.rest;
-        gxs |= (uint32_t)(int)(k.gx + 1.f) << (2 * i);
-        gys |= (uint32_t)(int)(k.gy + 1.f) << (2 * i);
+    for (int p = p0 + 1 + first; p < p1; p += stride) {
+      if (kRat) {
+        const float4 rt = ld(a.sink, si_at(2 * p, S, s));
+        const float d = ld(a.wire, si_at(p, S, s)).x;
+        acc[R_E0] = fmaxf(acc[R_E0], rt.x - d);
+        acc[R_E1] = fmaxf(acc[R_E1], rt.y - d);
+        acc[R_L0] = fminf(acc[R_L0], rt.z - d);
+        acc[R_L1] = fminf(acc[R_L1], rt.w - d);
+      }
+      if (kGrad) {
+        const float4 aj = ld(a.sink, si_at(2 * p + 1, S, s));
+        acc[A_R] += aj.x;
+        acc[A_F] += aj.y;
+        acc[Q_R] += aj.z;
+        acc[Q_F] += aj.w;
       }
     }
   }
-  const bool leader = !kHeavy || (int)threadIdx.x < lanes;
   if (kHeavy) {
     // Tree over the threads of each snapshot (thread t and t + h meet while h >= lanes), in a
     // fixed order: the leaders end with the totals.
     const int t = (int)threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < N_ACC; ++i) sh[i * kB + t] = acc[i];
+    for (int i = i0; i < i1; ++i) sh[i * kB + t] = acc[i];
     for (int h = kB >> 1; h >= lanes; h >>= 1) {
       __syncthreads();
       if (t < h) {
-        acc[R_E0] = fmaxf(acc[R_E0], sh[R_E0 * kB + t + h]);
-        acc[R_E1] = fmaxf(acc[R_E1], sh[R_E1 * kB + t + h]);
-        acc[R_L0] = fminf(acc[R_L0], sh[R_L0 * kB + t + h]);
-        acc[R_L1] = fminf(acc[R_L1], sh[R_L1 * kB + t + h]);
 #pragma unroll
-        for (int i = A_R; i < N_ACC; ++i) acc[i] += sh[i * kB + t + h];
-        if (h > lanes) {
-#pragma unroll
-          for (int i = 0; i < N_ACC; ++i) sh[i * kB + t] = acc[i];
+        for (int i = i0; i < i1; ++i) {
+          const float o = sh[i * kB + t + h];
+          acc[i] = i <= R_E1 ? fmaxf(acc[i], o) : (i <= R_L1 ? fminf(acc[i], o) : acc[i] + o);
+          if (h > lanes) sh[i * kB + t] = acc[i];
         }
       }
     }
+    if (t >= lanes) return;
   }
-  float lbar = 0.f;
-  if (leader && ln.on) {
-    if (n >= a.N0)
-      lbar = cell_step_si<kGrad>(a, sl, n - a.N0 - sl.c0, s, ld(a.load, si_at(n, S, s)), acc, ag_d,
-                                 make_float2(sl_d.z, sl_d.w));
-    const uint32_t o0 = si_at(a.io_perm ? ld(a.io_perm, (uint32_t)p0) : p0, S, s);
-    if (a.at_out) store_stream(at32(a.at_out, o0), at_d);
-    if (a.slew_out) store_stream(at32(a.slew_out, o0), sl_d);
-    if (a.rat_out) store_stream(at32(a.rat_out, o0), make_float4(acc[R_E0], acc[R_E1], acc[R_L0], acc[R_L1]));
-    if (a.slack_out)
-      store_stream(at32(a.slack_out, o0),
-                   make_float4(at_d.x - acc[R_E0], at_d.y - acc[R_E1], acc[R_L0] - at_d.z, acc[R_L1] - at_d.w));
-    if (kGrad) {
-      const float cl = a.c * lbar;
-      if (a.dx) *at32(a.dx, o0) = -(acc[X_RS] + cl * acc[X_N]);
-      if (a.dy) *at32(a.dy, o0) = -(acc[Y_RS] + cl * acc[Y_N]);
-    }
-  }
-  if (kHeavy) {
-    if (leader) sh[N_ACC * kB + threadIdx.x] = lbar;
-    __syncthreads();
-    lbar = sh[N_ACC * kB + (threadIdx.x & (unsigned)(lanes - 1))];
-  }
-  // Elmore adjoint of every sink: the cached ones from LDS and their codes, the rest (beyond
-  // the cache) read again.
-  if (kGrad && ln.on && (a.dx || a.dy)) {
-    const float cl = a.c * lbar;
-    int p = p0 + 1 + first;
-    for (int i = 0; i < kCache && p < p1; ++i, p += stride) {
-      const uint32_t o = si_at(a.io_perm ? ld(a.io_perm, (uint32_t)p) : p, S, s);
-      const float rest = sh[(crow + i) * kB + threadIdx.x];
-      const float gx = (float)((int)((gxs >> (2 * i)) & 3u) - 1);
-      const float gy = (float)((int)((gys >> (2 * i)) & 3u) - 1);
-      if (a.dx) *at32(a.dx, o) = gx * (cl + rest);
-      if (a.dy) *at32(a.dy, o) = gy * (cl + rest);
-    }
-#pragma unroll 4
-    for (; p < p1; p += stride) {
-      float scratch[N_ACC] = {};
-      const SinkSi k = sink_si<kGrad>(a, p, s, at_d, sl_d, xd, yd, scratch, false);
-      if (a.dx) *at32(a.dx, k.o) = k.gx * (cl + k.rest);
-      if (a.dy) *at32(a.dy, k.o) = k.gy * (cl + k.rest);
-    }
-  }
+  if (!ln.on) return;
+  const float lbar = cell_step_si<kGrad, kRat>(a, sl, n - a.N0 - sl.c0, s, ld(a.load, si_at(n, S, s)), acc, ag_d, sl_d);
+  if (kGrad) *at32(reinterpret_cast<float*>(a.sink), lbar_at(p0, S, s)) = lbar;
 }
 
-// One backward level: the level's huge nets [nu0, ne) and heavy nets [nh0, nu0) first, a
+// One backward level l >= 1: the level's huge nets [nu0, ne) and heavy nets [nh0, nu0) first, a
 // workgroup per net and snapshot chunk, then the nets [nb, nh0), (64 >> sl2) per wave.
-template <bool kGrad, int kB>
+template <bool kGrad, bool kRat, int kB>
 __global__ __launch_bounds__(kB) void k_bwd_level_si(int nb, int nh0, int nu0, int ne, Slots sl, BwdSiArgs a) {
-  __shared__ float sh[(kGrad ? kSiRows : N_ACC + 1) * kB];   // the sink cache only with the gradient
+  __shared__ float sh[X_RS * kB];
   const int w = (int)(threadIdx.x >> 6);
   const int b = (int)blockIdx.x;
   const int hl2u = si_bwd_hl2(a.sl2, kB, true), hl2h = si_bwd_hl2(a.sl2, kB, false);
@@ -3678,15 +3583,143 @@ __global__ __launch_bounds__(kB) void k_bwd_level_si(int nb, int nh0, int nu0, i
   if (b < nbu + nbh) {
     if (blockIdx.y != 0) return;               // these workgroups cover their snapshots along x
     if (b < nbu)
-      bwd_net_si<kGrad, true, kB>(a, sl, nu0 + b / nchu, si_heavy_lane(hl2u, a.S, b % nchu), hl2u, sh);
+      bwd_net_si<kGrad, kRat, true, kB>(a, sl, nu0 + b / nchu, si_heavy_lane(hl2u, a.S, b % nchu), hl2u, sh);
     else
-      bwd_net_si<kGrad, true, kB>(a, sl, nh0 + (b - nbu) / nchh, si_heavy_lane(hl2h, a.S, (b - nbu) % nchh), hl2h, sh);
+      bwd_net_si<kGrad, kRat, true, kB>(a, sl, nh0 + (b - nbu) / nchh, si_heavy_lane(hl2h, a.S, (b - nbu) % nchh), hl2h,
+                                        sh);
     return;
   }
   const SiLane ln = si_lane(a.sl2, a.S, (b - nbu - nbh) * (kB / 64) + w);
   const int n = nb + ln.item;
   if (n >= nh0 || !ln.on) return;
-  bwd_net_si<kGrad, false, kB>(a, sl, n, ln, a.sl2, sh);
+  bwd_net_si<kGrad, kRat, false, kB>(a, sl, n, ln, a.sl2, sh);
+}
+
+// ---------------------------------------------------------------- backward outputs, snapshot lanes
+struct BwdOutSiArgs {
+  const int* __restrict__ net_off;
+  const float* __restrict__ pin_cap;
+  const int* __restrict__ io_perm;
+  const float* __restrict__ x;
+  const float* __restrict__ y;
+  const int* __restrict__ heavy;        // nets of kSiHeavy+1..kSiHuge sinks
+  const int* __restrict__ huge;         // nets of more than kSiHuge sinks
+  const float4* __restrict__ rec;
+  const float2* __restrict__ wire;
+  const float4* __restrict__ sink;
+  float4* __restrict__ at_out;
+  float4* __restrict__ slew_out;
+  float4* __restrict__ rat_out;
+  float4* __restrict__ slack_out;
+  float* __restrict__ dx;
+  float* __restrict__ dy;
+  int N, N0, S, sl2, n_heavy, n_huge;
+  int max_sinks;                        // nets with more sinks are a heavy workgroup's
+  float r, c;
+};
+
+__device__ __forceinline__ void pin_out_si(const BwdOutSiArgs& a, uint32_t o, const float4& at, const float4& sl) {
+  if (a.at_out) store_stream(at32(a.at_out, o), at);
+  if (a.slew_out) store_stream(at32(a.slew_out, o), sl);
+}
+__device__ __forceinline__ void pin_rat_si(const BwdOutSiArgs& a, uint32_t o, const float4& at, const float4& rt) {
+  if (a.rat_out) store_stream(at32(a.rat_out, o), rt);
+  if (a.slack_out) store_stream(at32(a.slack_out, o), make_float4(at.x - rt.x, at.y - rt.y, rt.z - at.z, rt.w - at.w));
+}
+
+// Outputs of net n for the lane's snapshot: its sinks in turn (split over the threads of a
+// snapshot in a heavy workgroup, whose sums the first thread takes in thread order), then its
+// driver.
+template <bool kGrad, bool kRat, bool kHeavy>
+__device__ __forceinline__ void out_net_si(const BwdOutSiArgs& a, int n, const SiLane& ln, int hl2, float* sh) {
+  constexpr int kRows = 8;                      // required times, X_RS, X_N, Y_RS, Y_N
+  const uint32_t S = (uint32_t)a.S;
+  const int lanes = 1 << hl2, stride = kHeavy ? kSiRcBlock / lanes : 1;
+  const int s = ln.on ? ln.s : 0;
+  const int p0 = ld(a.net_off, (uint32_t)n), p1 = ld(a.net_off, (uint32_t)n + 1u);
+  const float4 at_d = rec_at_si(a.rec, n, S, s), sl_d = rec_sl_si(a.rec, n, S, s);
+  const uint32_t o0 = si_at(a.io_perm ? ld(a.io_perm, (uint32_t)p0) : p0, S, s);
+  float xd = 0.f, yd = 0.f, cl = 0.f;
+  if (kGrad) {
+    xd = ld(a.x, o0);
+    yd = ld(a.y, o0);
+    if (n >= a.N0) cl = a.c * ld(reinterpret_cast<const float*>(a.sink), lbar_at(p0, S, s));
+  }
+  float acc[kRows] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f};
+  if (ln.on) {
+#pragma unroll 2
+    for (int p = p0 + 1 + (kHeavy ? ln.item : 0); p < p1; p += stride) {
+      const float2 w = ld(a.wire, si_at(p, S, s));
+      const uint32_t o = si_at(a.io_perm ? ld(a.io_perm, (uint32_t)p) : p, S, s);
+      const float4 ats = make_float4(at_d.x + w.x, at_d.y + w.x, at_d.z + w.x, at_d.w + w.x);
+      if (a.at_out || a.slew_out)
+        pin_out_si(a, o, ats, make_float4(sink_slew(sl_d.x, w.y), sink_slew(sl_d.y, w.y), sink_slew(sl_d.z, w.y),
+                                          sink_slew(sl_d.w, w.y)));
+      if (kRat) {
+        const float4 rt = ld(a.sink, si_at(2 * p, S, s));
+        pin_rat_si(a, o, ats, rt);
+        acc[0] = fmaxf(acc[0], rt.x - w.x);
+        acc[1] = fmaxf(acc[1], rt.y - w.x);
+        acc[2] = fminf(acc[2], rt.z - w.x);
+        acc[3] = fminf(acc[3], rt.w - w.x);
+      }
+      if (kGrad) {
+        const float4 aj = ld(a.sink, si_at(2 * p + 1, S, s));
+        const float xs = ld(a.x, o), ys = ld(a.y, o), cp = ld(a.pin_cap, (uint32_t)p);
+        const float len = fabsf(xs - xd) + fabsf(ys - yd);
+        // Adjoints of the wire's delay and impulse times d / d len (see sink_sum).
+        const float rest = ((aj.x + aj.y) + (aj.z + aj.w) * w.y) * (1e-3f * a.r * fmaf(a.c, len, cp));
+        const float gx = sgnf(xs - xd), gy = sgnf(ys - yd);
+        if (a.dx) *at32(a.dx, o) = gx * (cl + rest);
+        if (a.dy) *at32(a.dy, o) = gy * (cl + rest);
+        acc[4] += gx * rest;
+        acc[5] += gx;
+        acc[6] += gy * rest;
+        acc[7] += gy;
+      }
+    }
+  }
+  if (kHeavy) {
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) sh[i * kSiRcBlock + threadIdx.x] = acc[i];
+    __syncthreads();
+    if ((int)threadIdx.x >= lanes) return;
+    for (int t = (int)threadIdx.x + lanes; t < kSiRcBlock; t += lanes) {
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        const float v = sh[i * kSiRcBlock + t];
+        acc[i] = i < 2 ? fmaxf(acc[i], v) : (i < 4 ? fminf(acc[i], v) : acc[i] + v);
+      }
+    }
+  }
+  if (!ln.on) return;
+  pin_out_si(a, o0, at_d, sl_d);
+  if (kRat) pin_rat_si(a, o0, at_d, make_float4(acc[0], acc[1], acc[2], acc[3]));
+  if (kGrad && a.dx) *at32(a.dx, o0) = -(acc[4] + cl * acc[5]);
+  if (kGrad && a.dy) *at32(a.dy, o0) = -(acc[6] + cl * acc[7]);
+}
+
+// Outputs of every net after the last level, on the workgroups of k_rc_si.
+template <bool kGrad, bool kRat>
+__global__ __launch_bounds__(kSiRcBlock) void k_bwd_out_si(BwdOutSiArgs a) {
+  __shared__ float sh[8 * kSiRcBlock];
+  const int b = (int)blockIdx.x;
+  const int hl2u = min(a.sl2, 3), nchu = chunks_of(a.S, hl2u), nchh = chunks_of(a.S, a.sl2);
+  const int nbu = a.n_huge * nchu, nbh = a.n_heavy * nchh;
+  if (b < nbu + nbh) {
+    if (blockIdx.y != 0) return;               // these workgroups cover their snapshots along x
+    const int q = b - nbu;
+    if (q < 0)
+      out_net_si<kGrad, kRat, true>(a, ld(a.huge, (uint32_t)(b / nchu)), si_heavy_lane(hl2u, a.S, b % nchu), hl2u, sh);
+    else
+      out_net_si<kGrad, kRat, true>(a, ld(a.heavy, (uint32_t)(q / nchh)), si_heavy_lane(a.sl2, a.S, q % nchh), a.sl2, sh);
+    return;
+  }
+  const SiLane ln = si_lane(a.sl2, a.S, (b - nbu - nbh) * (kSiRcBlock / 64) + (int)(threadIdx.x >> 6));
+  const int n = ln.item;
+  if (n >= a.N || !ln.on) return;
+  if (ld(a.net_off, (uint32_t)n + 1u) - ld(a.net_off, (uint32_t)n) - 1 > a.max_sinks) return;   // a heavy workgroup's
+  out_net_si<kGrad, kRat, false>(a, n, ln, a.sl2, sh);
 }
 
 }  // namespace
@@ -3871,35 +3904,45 @@ sta_status launch_backward_si(sta_graph* g, const float* x, const float* y, cons
     LaunchTimer t(g, s, STA_K_EP_SEED);
     k_ep_seed_si<<<dim3(si_blocks(g->E, D.sl2, kWavesPerBlock), D.gy), kBlock, 0, s>>>(ea);
   }
-  const BwdSiArgs ba{d.net_off, d.pin_cap, d.ell, io, x, y, d.lut_grid, d.lut_coef, lut_keys(g),
+  const bool rat = out->rat || out->slack || !grad;
+  const BwdSiArgs ba{d.net_off, d.ell, d.lut_grid, d.lut_coef, lut_keys(g),
                      reinterpret_cast<const float4*>(sb + S * g->state.rec),
                      reinterpret_cast<const float2*>(sb + S * g->state.wire),
-                     reinterpret_cast<const float*>(sb + S * g->state.load), sink,
-                     reinterpret_cast<float4*>(out->at), reinterpret_cast<float4*>(out->slew),
-                     reinterpret_cast<float4*>(out->rat), reinterpret_cast<float4*>(out->slack), out->dx, out->dy,
-                     g->N0, D.S, D.sl2, g->cons.r_per_um, g->cons.c_per_um, grad ? 1.0f / gamma_ps : 0.f};
+                     reinterpret_cast<const float*>(sb + S * g->state.load), sink, g->N0, D.S, D.sl2,
+                     grad ? 1.0f / gamma_ps : 0.f};
+  const int nh = D.split ? (int)g->si_heavy.size() : 0, nu = D.split ? (int)g->si_huge.size() : 0;
+  const BwdOutSiArgs oa{d.net_off, d.pin_cap, io, x, y, d.si_heavy, d.si_huge, ba.rec, ba.wire, sink,
+                        reinterpret_cast<float4*>(out->at), reinterpret_cast<float4*>(out->slew),
+                        reinterpret_cast<float4*>(out->rat), reinterpret_cast<float4*>(out->slack), out->dx, out->dy,
+                        g->N, g->N0, D.S, D.sl2, nh, nu, D.split ? kSiHeavy : INT32_MAX, g->cons.r_per_um,
+                        g->cons.c_per_um};
   const int kb = g->sched_cfg.lane_block;    // 256, 512 or 1024 (sta_set_schedule checks)
-  for (int l = g->L - 1; l >= 0; --l) {
-    const int lo = g->level_off[l], hi = g->level_off[l + 1];
-    const int hs = D.split ? g->si_hs[l] : hi, us = D.split ? g->si_us[l] : hi;
-    if (hi == lo) continue;
-    const int uch = (D.S + (1 << si_bwd_hl2(D.sl2, kb, true)) - 1) >> si_bwd_hl2(D.sl2, kb, true);
-    const int hch = (D.S + (1 << si_bwd_hl2(D.sl2, kb, false)) - 1) >> si_bwd_hl2(D.sl2, kb, false);
-    const unsigned blocks = (unsigned)((hi - us) * uch + (us - hs) * hch) + si_blocks(hs - lo, D.sl2, kb / 64);
-    LaunchTimer t(g, s, STA_K_BWD_LEVEL);
-    const Slots sl = level_slots(g, l);
-    const dim3 grid(blocks, D.gy);
-    if (kb == 256) {
-      if (grad) k_bwd_level_si<true, 256><<<grid, 256, 0, s>>>(lo, hs, us, hi, sl, ba);
-      else k_bwd_level_si<false, 256><<<grid, 256, 0, s>>>(lo, hs, us, hi, sl, ba);
-    } else if (kb == 1024) {
-      if (grad) k_bwd_level_si<true, 1024><<<grid, 1024, 0, s>>>(lo, hs, us, hi, sl, ba);
-      else k_bwd_level_si<false, 1024><<<grid, 1024, 0, s>>>(lo, hs, us, hi, sl, ba);
-    } else {
-      if (grad) k_bwd_level_si<true, 512><<<grid, 512, 0, s>>>(lo, hs, us, hi, sl, ba);
-      else k_bwd_level_si<false, 512><<<grid, 512, 0, s>>>(lo, hs, us, hi, sl, ba);
+  auto sweep = [&](auto level, auto outputs) {
+    for (int l = g->L - 1; l >= 1; --l) {
+      const int lo = g->level_off[l], hi = g->level_off[l + 1];
+      const int hs = D.split ? g->si_hs[l] : hi, us = D.split ? g->si_us[l] : hi;
+      if (hi == lo) continue;
+      const int uch = chunks_of(D.S, si_bwd_hl2(D.sl2, kb, true)), hch = chunks_of(D.S, si_bwd_hl2(D.sl2, kb, false));
+      const unsigned blocks = (unsigned)((hi - us) * uch + (us - hs) * hch) + si_blocks(hs - lo, D.sl2, kb / 64);
+      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+      level<<<dim3(blocks, D.gy), kb, 0, s>>>(lo, hs, us, hi, level_slots(g, l), ba);
     }
-  }
+    LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+    outputs<<<dim3((unsigned)(nh * D.hch + nu * D.uch) + si_blocks(g->N, D.sl2, kSiRcBlock / 64), D.gy), kSiRcBlock, 0,
+              s>>>(oa);
+  };
+  if (!grad)
+    kb == 256 ? sweep(k_bwd_level_si<false, true, 256>, k_bwd_out_si<false, true>)
+    : kb == 512 ? sweep(k_bwd_level_si<false, true, 512>, k_bwd_out_si<false, true>)
+                : sweep(k_bwd_level_si<false, true, 1024>, k_bwd_out_si<false, true>);
+  else if (rat)
+    kb == 256 ? sweep(k_bwd_level_si<true, true, 256>, k_bwd_out_si<true, true>)
+    : kb == 512 ? sweep(k_bwd_level_si<true, true, 512>, k_bwd_out_si<true, true>)
+                : sweep(k_bwd_level_si<true, true, 1024>, k_bwd_out_si<true, true>);
+  else
+    kb == 256 ? sweep(k_bwd_level_si<true, false, 256>, k_bwd_out_si<true, false>)
+    : kb == 512 ? sweep(k_bwd_level_si<true, false, 512>, k_bwd_out_si<true, false>)
+                : sweep(k_bwd_level_si<true, false, 1024>, k_bwd_out_si<true, false>);
   if (g->profiling) end_run(g, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "backward launch");
