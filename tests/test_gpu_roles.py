@@ -1,0 +1,100 @@
+"""Backward sweep split by role against the fused level kernel, its passes without required times or
+without the gradient, and RC-tree chunks at the edges of their packing."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from gen.netlist import jitter, make_design, scaled_spec
+from oracle import sta_oracle as O
+from paper_2603_28381_amd import Graph
+from tests._designs import fanout_design, wide_dag
+from tests.test_gpu_parity import GAMMA, check_grad, check_values, gpu_run
+
+pytestmark = pytest.mark.gpu
+
+KINDS = [dict(rat=True, grad=True), dict(rat=False, grad=True), dict(rat=True, grad=False)]
+
+
+def _sweep(g, x, y, wns=False, pins=True, **kind):
+    f = g.forward(x, y, gamma=GAMMA)
+    o = g.backward(x, y, f, wns=wns, pins=pins, **kind)
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in o.items()}
+
+
+@pytest.mark.parametrize("design", ["tail", "wide", "fanout"])
+@pytest.mark.parametrize("kind", range(3))
+def test_split_levels_equal_fused_bitwise(design, kind):
+    # Checkpointing in one segment runs the fused kernel over the same records: heavy-tailed nets
+    # (every class and whole workgroups), cells of 5-8 inputs, a net of over 512 sinks.
+    d = {"tail": lambda: make_design(scaled_spec(30_000, cfg_id=81, box_um=400.0)),
+         "wide": lambda: wide_dag(n_levels=9, gates_per_level=70, n_pi=16, seed=5),
+         "fanout": lambda: fanout_design(via_cell=True)}[design]()
+    g = Graph.from_design(d)
+    g.levelize()
+    x, y = torch.tensor(d.x, device="cuda"), torch.tensor(d.y, device="cuda")
+    print(f"roles: {design} {KINDS[kind]}", flush=True)
+    split = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
+    g.set_checkpointing(1000)
+    fused = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
+    assert set(split) == set(fused)
+    for k in split:
+        assert np.array_equal(split[k], fused[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("kind,S", [(0, 24), (1, 40), (2, 24)])
+def test_snapshots_past_the_split_rule_equal_one_call_bitwise(kind, S):
+    # Enough snapshots that a level's nets pass the line of the fused kernel, which one does not.
+    d = make_design(scaled_spec(60_000, cfg_id=82, box_um=500.0))
+    snaps = [jitter(d, 3.0, stream=s) for s in range(S)]
+    g = Graph.from_design(d)
+    L = g.levelize()
+    line = 16384 if kind == 1 else 10000
+    assert S * d.n_nets // L > line > d.n_nets // L
+    alone = {}
+    for s in (0, S - 1):
+        alone[s] = _sweep(g, torch.tensor(snaps[s][0], device="cuda"), torch.tensor(snaps[s][1], device="cuda"), **KINDS[kind])
+    g.set_snapshots(S)
+    x = torch.tensor(np.stack([a for a, _ in snaps]), device="cuda")
+    y = torch.tensor(np.stack([b for _, b in snaps]), device="cuda")
+    many = _sweep(g, x, y, **KINDS[kind])
+    for s, ref in alone.items():
+        for k in ref:
+            assert np.array_equal(many[k][s], ref[k], equal_nan=True), (s, k)
+
+
+@pytest.mark.parametrize("S", [1, 5, 64])
+def test_snapshot_lane_passes_equal_the_full_sweep_bitwise(S):
+    # S = 1: the same kernels under one thread per net.
+    d = make_design(scaled_spec(12_000, cfg_id=83, box_um=300.0))
+    g = Graph.from_design(d)
+    g.levelize()
+    if S == 1:
+        g.set_schedule(2, 2, 64, level_scheme="thread")
+        x, y = torch.tensor(d.x, device="cuda"), torch.tensor(d.y, device="cuda")
+    else:
+        g.set_snapshots(S)
+        g.set_snapshot_layout(True)
+        snaps = [jitter(d, 3.0, stream=s) for s in range(S)]
+        x = torch.tensor(np.stack([a for a, _ in snaps], 1), device="cuda")
+        y = torch.tensor(np.stack([b for _, b in snaps], 1), device="cuda")
+    full = _sweep(g, x, y, **KINDS[0])
+    for kind in KINDS[1:]:
+        part = _sweep(g, x, y, pins=kind["rat"], **kind)
+        for k in part:
+            assert np.array_equal(part[k], full[k], equal_nan=True), (kind, k)
+
+
+@pytest.mark.parametrize("pins", [255, 256, 257, 512, 1023, 1024, 1025])
+def test_tree_chunk_packing_edges(pins):
+    # One net of `pins` pins (a chunk of its own from 257 on, the fallback kernel from 1025) as a
+    # binary heap, among the small nets of its buffers.
+    from gen.netlist import heap_trees
+    d = heap_trees(fanout_design(n_sinks=pins - 1, via_cell=True))
+    assert np.diff(d.net_offsets).max() == pins
+    got = gpu_run(d)
+    ref = O.run(d, gamma=GAMMA, grad="tns")
+    check_values(d, got, ref)
+    check_grad(got, ref, 1e-3, 1e-6)
