@@ -3462,46 +3462,60 @@ __device__ __forceinline__ float2 rec_late_slew_si(const float4* __restrict__ re
   return ld(reinterpret_cast<const float2*>(rec), 2u * si_at(kRecChunks * r + 1, S, s) + 1u);
 }
 
-// Cell step of cell kc in snapshot s, one pass over its arcs: the inputs' required times (kRat), and
+// What the cell step reads of one input, loaded apart from its use, so that the first inputs' loads
+// are in flight while the net step walks its sinks.
+struct CellInSi {
+  int4 e;
+  float2 w, iag;   // wire, smoothed arrivals of the source
+  float4 isl;      // slews of the source (the late ones without kRat)
+};
+template <bool kGrad, bool kRat>
+__device__ __forceinline__ CellInSi cell_in_si(const BwdSiArgs& a, const Slots& sl, int kc, int j, int s) {
+  const uint32_t S = (uint32_t)a.S;
+  CellInSi in;
+  in.e = ld(a.ell, (uint32_t)(sl.base + min(j, sl.F - 1) * sl.nc + kc));
+  if (j >= sl.F) in.e.x = -1;
+  const int src = max(in.e.x, 0);              // empty slots name record 0 and pin 0
+  in.w = ld(a.wire, si_at(in.e.y, S, s));
+  if (kRat) {
+    in.isl = rec_sl_si(a.rec, src, S, s);
+  } else {
+    const float2 late = rec_late_slew_si(a.rec, src, S, s);
+    in.isl = make_float4(0.f, 0.f, late.x, late.y);
+  }
+  in.iag = kGrad ? rec_ag_si(a.rec, src, S, s) : make_float2(0.f, 0.f);
+  return in;
+}
+
+// Cell step of a cell in snapshot s, one pass over its arcs: the inputs' required times (kRat), and
 // with the gradient the split of the driver's adjoint over the arcs and the slew and load
 // adjoints, which it returns.  The softmax weight of an arc is exp((x_j - ATg) / gamma), with
 // ATg the driver's smoothed arrival that the forward kept (its maximum plus gamma times the log
 // of its sum, Eq. 4); the slew adjoint goes to the first arc whose output slew equals the
 // driver's kept worst slew (the forward took that maximum over the same lookups, bit for bit).
-template <bool kGrad, bool kRat>
-__device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, const Slots& sl, int kc, int s, float load,
-                                              const float (&acc)[N_ACC], float2 atg, float2 worst) {
+template <bool kGrad, bool kRat, class Inputs>
+__device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, int F, int s, float load, const float (&acc)[N_ACC],
+                                              float2 atg, float2 worst, Inputs input) {
   const uint32_t S = (uint32_t)a.S;
   const float rat_o[4] = {acc[R_E0], acc[R_E1], acc[R_L0], acc[R_L1]};
   const float abar[2] = {acc[A_R], acc[A_F]}, sbar[2] = {acc[Q_R] * worst.x, acc[Q_F] * worst.y};
   const float ag[2] = {atg.x, atg.y}, smax[2] = {worst.x, worst.y};
   bool open[2] = {true, true};    // the worst-slew arc of the transition not met yet
   float lb[2] = {0.f, 0.f};
-#pragma unroll 2
-  for (int j = 0; j < sl.F; ++j) {
-    const int4 e = ld(a.ell, (uint32_t)(sl.base + j * sl.nc + kc));
-    if (e.x < 0) continue;
+  auto arc = [&](const CellInSi& in) {
+    const int4 e = in.e;
+    if (e.x < 0) return;
     const bool same = ell_positive(e);
-    const float2 w = ld(a.wire, si_at(e.y, S, s));
-    float4 isl = make_float4(0.f, 0.f, 0.f, 0.f);               // the input's slews
-    if (kRat) {
-      isl = rec_sl_si(a.rec, e.x, S, s);
-    } else {
-      const float2 late = rec_late_slew_si(a.rec, e.x, S, s);
-      isl.z = late.x;
-      isl.w = late.y;
-    }
-    const float2 iag = kGrad ? rec_ag_si(a.rec, e.x, S, s) : make_float2(0.f, 0.f);
     float4 rat_in = make_float4(0.f, 0.f, 0.f, 0.f), adj_in = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = kRat ? 0 : 2; k < 4; ++k) {
       const int m = k >> 1, t = k & 1;
       const int tp = same ? t : 1 - t;
-      const float slew = sink_slew(plane_pick(isl, m, same, t), w.y);
+      const float slew = sink_slew(plane_pick(in.isl, m, same, t), in.w.y);
       const LutVal v = lut_eval_si<kGrad>(a.grid, a.coef, a.keys, ell_arc(e), t, slew, load);
       if (kRat) set_comp(rat_in, 2 * m + tp, rat_o[k] - v.d);
       if (kGrad && m == 1) {
-        const float xg = (((same == (t == 0)) ? iag.x : iag.y) + w.x) + v.d;
+        const float xg = (((same == (t == 0)) ? in.iag.x : in.iag.y) + in.w.x) + v.d;
         const float dbar = fexp((xg - ag[t]) * a.inv_gamma) * abar[t];
         const bool star = open[t] && v.s == smax[t];
         open[t] = open[t] && !star;
@@ -3513,7 +3527,8 @@ __device__ __forceinline__ float cell_step_si(const BwdSiArgs& a, const Slots& s
     }
     if (kRat) *at32(a.sink, si_at(2 * e.y, S, s)) = rat_in;
     if (kGrad) *at32(a.sink, si_at(2 * e.y + 1, S, s)) = adj_in;
-  }
+  };
+  input(F, arc);
   return lb[0] + lb[1];
 }
 
@@ -3524,11 +3539,20 @@ template <bool kGrad, bool kRat, bool kHeavy, int kB>
 __device__ __forceinline__ void bwd_net_si(const BwdSiArgs& a, const Slots& sl, int n, const SiLane& ln, int hl2,
                                            float* sh) {
   constexpr int i0 = kRat ? 0 : (int)A_R, i1 = kGrad ? (int)X_RS : (int)A_R;   // reductions in use
+  // Inputs loaded before the sinks: all four of most cells (64 snapshots of 841k pins 3937 -> 3815 us
+  // a step, of 108k pins 1029 -> 973, 32 of 215k 1159 -> 1075).  Workgroups of 1024 threads fit a CU
+  // once with those registers and keep none (4213 us, 4425 with them).
+  constexpr int kPre = kB <= 512 ? kArcLanes : 0;
   const uint32_t S = (uint32_t)a.S;
   const int s = ln.on ? ln.s : 0;
   const int p0 = ld(a.net_off, (uint32_t)n), p1 = ld(a.net_off, (uint32_t)n + 1u);
   const float2 sl_d = kGrad ? rec_late_slew_si(a.rec, n, S, s) : make_float2(0.f, 0.f);
   const float2 ag_d = kGrad ? rec_ag_si(a.rec, n, S, s) : make_float2(0.f, 0.f);
+  const int kc = n - a.N0 - sl.c0;
+  const float load = ld(a.load, si_at(n, S, s));
+  CellInSi early[kPre > 0 ? kPre : 1];
+#pragma unroll
+  for (int i = 0; i < kPre; ++i) early[i] = cell_in_si<kGrad, kRat>(a, sl, kc, i, s);
   float acc[N_ACC] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const int lanes = 1 << hl2;                   // heavy workgroups: snapshots per workgroup
   const int first = kHeavy ? ln.item : 0;
@@ -3573,7 +3597,11 @@ __device__ __forceinline__ void bwd_net_si(const BwdSiArgs& a, const Slots& sl, 
     if (t >= lanes) return;
   }
   if (!ln.on) return;
-  const float lbar = cell_step_si<kGrad, kRat>(a, sl, n - a.N0 - sl.c0, s, ld(a.load, si_at(n, S, s)), acc, ag_d, sl_d);
+  const float lbar = cell_step_si<kGrad, kRat>(a, sl.F, s, load, acc, ag_d, sl_d, [&](int F, auto arc) {
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) arc(early[i]);
+    for (int j = kPre; j < F; ++j) arc(cell_in_si<kGrad, kRat>(a, sl, kc, j, s));
+  });
   if (kGrad) *at32(reinterpret_cast<float*>(a.sink), lbar_at(p0, S, s)) = lbar;
 }
 
