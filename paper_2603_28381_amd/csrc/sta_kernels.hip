@@ -1787,11 +1787,12 @@ __device__ __forceinline__ float sum_arcs(const float (&v)[NA]) {
   else return (v[0] + v[1]) + (v[2] + v[3]);
 }
 
-// Adjoint of the root load: uv = {U_r, U_f, V_r, V_f}, per output transition the softmax-weighted
-// d delay / d load over the arcs and d slew / d load of the worst-slew arc, times the driver's
-// adjoints.
+// One output transition's part of the root load's adjoint: the driver's adjoints times U, the
+// softmax-weighted d delay / d load over the arcs, and V, d slew / d load of the worst-slew arc.
+__device__ __forceinline__ float load_part(float abar, float u, float sbar, float v) { return fmaf(abar, u, sbar * v); }
+// The root load's adjoint from uv = {U_r, U_f, V_r, V_f}.
 __device__ __forceinline__ float load_adjoint(const float4& uv, float a_r, float a_f, float s_r, float s_f) {
-  return fmaf(a_r, uv.x, fmaf(a_f, uv.y, fmaf(s_r, uv.z, s_f * uv.w)));
+  return load_part(a_r, uv.x, s_r, uv.z) + load_part(a_f, uv.y, s_f, uv.w);
 }
 
 // Group-wide reduction of the net-step accumulators (G = 16/32/64 wave groups, or a whole
@@ -1988,10 +1989,10 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
   const float inv_z = frcp(z);
   float lu = 0.f, lv = 0.f;                    // load partials U, V of the condition's transition
   for (int j0 = 0; j0 < sl.F; j0 += kArcLanes) {
-    float u[NA], vv[NA];
+    float u[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      u[i] = vv[i] = 0.f;
+      u[i] = 0.f;
       ArcBwd v = arc0[i];
       if (j0 > 0) {
         v.valid = false;
@@ -2009,33 +2010,29 @@ __device__ __forceinline__ void bwd_net(const BwdArgs& a, const Slots& sl, const
           *at32(sw, aj + (uint32_t)v.tp) = dbar;
           *at32(sw, aj + 2u + (uint32_t)v.tp) = fmaf(dbar, v.ddx, star ? sbar * v.dsx : 0.f);
           u[i] = wj * v.ddy;
-          vv[i] = star ? v.dsy : 0.f;
+          lv = star ? v.dsy : lv;
         }
       }
     }
-    if (kGrad) {
-      lu += arc_reduce<kSum, AL>(sum_arcs<NA>(u));
-      lv += arc_reduce<kSum, AL>(sum_arcs<NA>(vv));
-    }
+    if (kGrad) lu += arc_reduce<kSum, AL>(sum_arcs<NA>(u));
   }
+  if (kGrad) lv = arc_reduce<kSum, AL>(lv);    // one arc's, the others zero
 
   // 3. Load adjoint of the root from the load partials of late rise and late fall (cell
   //    lanes 2 * AL and 3 * AL).
   float lbar = 0.f;
   if (kGrad) {
-    float4 uv;
+    const float lb = load_part(abar, lu, sbar, lv);
     if (!block) {
       const int base = (threadIdx.x & 63) & ~(G - 1);
-      uv = make_float4(__shfl(lu, base + 2 * AL), __shfl(lu, base + 3 * AL), __shfl(lv, base + 2 * AL),
-                       __shfl(lv, base + 3 * AL));
+      lbar = __shfl(lb, base + 2 * AL) + __shfl(lb, base + 3 * AL);
     } else {
-      if (threadIdx.x == 2 * AL) { sh[0] = lu; sh[2] = lv; }
-      if (threadIdx.x == 3 * AL) { sh[1] = lu; sh[3] = lv; }
+      if (threadIdx.x == 2 * AL) sh[0] = lb;
+      if (threadIdx.x == 3 * AL) sh[1] = lb;
       __syncthreads();
-      uv = make_float4(sh[0], sh[1], sh[2], sh[3]);
+      lbar = sh[0] + sh[1];
       __syncthreads();
     }
-    lbar = load_adjoint(uv, acc[A_R], acc[A_F], sb_r, sb_f);
   }
   if (!gs.active) return;
   if (kGrad && (a.dx || a.dy) && !a.tree_adj) {
@@ -2140,7 +2137,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level(int nh, int h0, int e0, in
 //   after:  {RAT(output) - D}, {W A, W A B + (worst-slew arc: S C)}.
 // The slot of a net's driver pin, which no sink uses, holds {U_r, U_f, V_r, V_f} (load_adjoint)
 // and {C_r, C_f} (d slew / d slew over the sink's slew, of the worst-slew arc), by output
-// transition.  Every value is computed by the operations of k_bwd_level in the same order, so
+// transition; under checkpointing, where drivers have no slot and records may be written, they
+// take words of the net's record that no kernel reads: U and V the last two of its early
+// chunks, C the last of its late ones.  Every value is computed by the operations of k_bwd_level in the same order, so
 // both give the same bits.
 
 // Which net a thread serves, as level_slot, with the smallest group 2^g0 known at run time.
@@ -2207,7 +2206,7 @@ __device__ __forceinline__ void reduce_step(float (&v)[N_ACC], bool block, float
 // Chain role of one net of level >= 1: two round trips of loads - {pin range, cell-input
 // slots}, then {sinks, own inputs' slots} - a reduction of at most eight values, and the
 // inputs' slots rewritten in place.  Lane j takes input j for all its conditions.
-template <int G, bool kGrad, bool kRat>
+template <int G, bool kGrad, bool kRat, bool kCkpt>
 __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, const GroupSlot& gs, float* sh) {
   const int gl = gs.gl;
   const bool block = gs.block;
@@ -2215,33 +2214,37 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
   const int kc = n - a.N0 - sl.c0;
   const int p0 = ld(a.net_off, (uint32_t)n);
   const int p1v = ld(a.net_off, (uint32_t)n + 1u);
-  const int2* ell2 = reinterpret_cast<const int2*>(a.ell);   // second half: {arc with the sign, slot}
   const bool in0 = gs.active && gl < sl.F;
-  int2 e = ld(ell2, 2u * (uint32_t)(sl.base + (in0 ? gl * sl.nc : 0) + kc) + 1u);
+  int4 e = ld(a.ell, (uint32_t)(sl.base + (in0 ? gl * sl.nc : 0) + kc));
+  const int r = kCkpt ? ld(a.loc, (uint32_t)n) : n;          // the net's record
+  const int sk0 = kCkpt ? ld(a.sink_base, (uint32_t)n) - (p0 + 1) : 0;
+  const float* rec = reinterpret_cast<const float*>(a.rec);
   float sl_r = 0.f, sl_f = 0.f;
   if (kGrad) {
-    const float* rec = reinterpret_cast<const float*>(a.rec);
-    sl_r = ld(rec, 4u * (uint32_t)(kRecChunks * n + 2) + 1u);
-    sl_f = ld(rec, 4u * (uint32_t)(kRecChunks * n + 3) + 1u);
+    sl_r = ld(rec, 4u * (uint32_t)(kRecChunks * r + 2) + 1u);
+    sl_f = ld(rec, 4u * (uint32_t)(kRecChunks * r + 3) + 1u);
   }
   const int p1 = gs.active ? p1v : p0;
-  // An empty input slot of the padded layout names pin 0, the driver of net 0: no input's slot.
-  bool has = in0 && e.y != 0;
+  bool has = in0 && e.x >= 0;
   float4 d = make_float4(0.f, 0.f, 0.f, 0.f), wb = d;
   float2 cst = make_float2(0.f, 0.f);
   const int stride = block ? kBlock : G;
   const int s0 = p0 + 1 + gl;
   const bool h0 = s0 < p1;
-  const uint32_t u0 = h0 ? (uint32_t)s0 : 0u;
+  const uint32_t u0 = h0 ? (uint32_t)(sk0 + s0) : 0u;
   float4 rt = d, aj = d;
   if (kRat) rt = ld(a.sink, rat_at(u0));
   if (kGrad) aj = ld(a.sink, adj_at(u0));
   const float w0 = kRat ? ld(a.wire, u0).x : 0.f;
-  if (kRat) d = ld(a.sink, rat_at((uint32_t)e.y));
+  if (kRat) d = ld(a.sink, rat_at((uint32_t)e.w));
   if (kGrad) {
-    wb = ld(a.sink, adj_at((uint32_t)e.y));
-    const float4 c4 = ld(a.sink, adj_at((uint32_t)p0));
-    cst = make_float2(c4.x, c4.y);
+    wb = ld(a.sink, adj_at((uint32_t)e.w));
+    if (kCkpt) {
+      cst = make_float2(ld(rec, 4u * (uint32_t)(kRecChunks * r + 2) + 3u), ld(rec, 4u * (uint32_t)(kRecChunks * r + 3) + 3u));
+    } else {
+      const float4 c4 = ld(a.sink, adj_at((uint32_t)p0));
+      cst = make_float2(c4.x, c4.y);
+    }
   }
   float acc[N_ACC] = {-kInf, -kInf, kInf, kInf, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   auto take = [&](const float4& r, const float4& j, float w) {
@@ -2261,7 +2264,7 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
   if (h0) take(rt, aj, w0);
   if (block) {
     for (int p = s0 + stride; p < p1; p += stride) {
-      const uint32_t u = (uint32_t)p;
+      const uint32_t u = (uint32_t)(sk0 + p);
       float4 r2 = rt, j2 = aj;
       if (kRat) r2 = ld(a.sink, rat_at(u));
       if (kGrad) j2 = ld(a.sink, adj_at(u));
@@ -2273,15 +2276,15 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
   const float sc_f = kGrad ? acc[Q_F] * sl_f * cst.y : 0.f;
   for (int j = gl; gs.active && j < sl.F; j += stride) {
     if (j != gl) {                             // more inputs than lanes
-      e = ld(ell2, 2u * (uint32_t)(sl.base + j * sl.nc + kc) + 1u);
-      has = e.y != 0;
-      if (kRat) d = ld(a.sink, rat_at((uint32_t)e.y));
-      if (kGrad) wb = ld(a.sink, adj_at((uint32_t)e.y));
+      e = ld(a.ell, (uint32_t)(sl.base + j * sl.nc + kc));
+      has = e.x >= 0;
+      if (kRat) d = ld(a.sink, rat_at((uint32_t)e.w));
+      if (kGrad) wb = ld(a.sink, adj_at((uint32_t)e.w));
     }
     if (!has) break;                           // a cell's inputs fill its first slots
-    const bool flip = e.x < 0;
+    const bool flip = !ell_positive(e);
     if (kRat)
-      *at32(a.sink, rat_at((uint32_t)e.y)) =
+      *at32(a.sink, rat_at((uint32_t)e.w)) =
           make_float4((flip ? acc[R_E1] : acc[R_E0]) - d.x, (flip ? acc[R_E0] : acc[R_E1]) - d.y,
                       (flip ? acc[R_L1] : acc[R_L0]) - d.z, (flip ? acc[R_L0] : acc[R_L1]) - d.w);
     if (kGrad) {
@@ -2289,7 +2292,7 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
       const float d_f = fabsf(wb.y) * (flip ? acc[A_R] : acc[A_F]);
       const float s_r = __builtin_signbit(wb.x) ? (flip ? sc_f : sc_r) : 0.f;
       const float s_f = __builtin_signbit(wb.y) ? (flip ? sc_r : sc_f) : 0.f;
-      *at32(a.sink, adj_at((uint32_t)e.y)) = make_float4(d_r, d_f, fmaf(d_r, wb.z, s_r), fmaf(d_f, wb.w, s_f));
+      *at32(a.sink, adj_at((uint32_t)e.w)) = make_float4(d_r, d_f, fmaf(d_r, wb.z, s_r), fmaf(d_f, wb.w, s_f));
     }
   }
 }
@@ -2298,14 +2301,15 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
 // Bound by memory: 2.6M pins in canonical order with every output take 84 us with plain stores (368
 // MB, 4.4 TB/s; a 4 GiB copy reaches 4.8), 103 us with streaming ones, which leave L2 before a
 // line's pieces - its sinks' and its drivers' - have met there.
-template <int G, bool kGrad, bool kRat>
+template <int G, bool kGrad, bool kRat, bool kCkpt>
 __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, float* sh) {
   const int gl = gs.gl;
   const bool block = gs.block;
   const int n = gs.active ? gs.entry : 0;
   const int p0 = ld(a.net_off, (uint32_t)n);
   const int p1v = ld(a.net_off, (uint32_t)n + 1u);
-  const uint32_t rs = (uint32_t)(kRecChunks * n);
+  const uint32_t rs = (uint32_t)(kRecChunks * (kCkpt ? ld(a.loc, (uint32_t)n) : n));
+  const int sk0 = kCkpt ? ld(a.sink_base, (uint32_t)n) - (p0 + 1) : 0;
   const float4 c0 = ld(a.rec, rs), c1 = ld(a.rec, rs + 1), c2 = ld(a.rec, rs + 2), c3 = ld(a.rec, rs + 3);
   const float4 at_d = make_float4(c0.x, c1.x, c2.x, c3.x);
   const float4 sl_d = make_float4(c0.y, c1.y, c2.y, c3.y);
@@ -2317,13 +2321,14 @@ __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, 
   if (kGrad) {
     xd = ld(a.x, qd);
     yd = ld(a.y, qd);
-    if (n >= a.N0) uv = ld(a.sink, rat_at((uint32_t)p0));
+    if (n >= a.N0) uv = kCkpt ? make_float4(c0.z, c0.w, c1.z, c1.w) : ld(a.sink, rat_at((uint32_t)p0));
   }
   const int stride = block ? kBlock : G;
   const int s0 = p0 + 1 + gl;
   const bool has0 = s0 < p1, has1 = block && s0 + stride < p1;
   auto load = [&](int p) {
-    return canon ? sink_load<true, kGrad, kRat>(a, p, p) : sink_load<false, kGrad, kRat>(a, p, p);
+    const int slot = kCkpt ? max(sk0 + p, 0) : p;   // of lanes past the sinks: any
+    return canon ? sink_load<true, kGrad, kRat>(a, p, slot) : sink_load<false, kGrad, kRat>(a, p, slot);
   };
   const SinkIn in0 = load(has0 ? s0 : p0);
   SinkIn in1{};
@@ -2398,7 +2403,7 @@ __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, 
 // Cells role: 16 lanes per cell, lane (k, jl) one lookup for condition k and arc jl, as the
 // forward level; cells of 5-8 inputs take a second arc per lane.  Lanes of the early
 // conditions only serve the required times.
-template <bool kGrad, bool kRat>
+template <bool kGrad, bool kRat, bool kCkpt>
 __device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int gid) {
   const int kc = gid / kCellLanes;
   if (kc >= sl.nc) return;                     // uniform over the cell's 16 lanes
@@ -2409,7 +2414,7 @@ __device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int 
   const int4 e0 = ld(a.ell, (uint32_t)(sl.base + min(jl, sl.F - 1) * sl.nc + kc));
   const float load = ld(a.load, (uint32_t)n);
   uint32_t p0 = 0;
-  if (kGrad) p0 = (uint32_t)ld(a.net_off, (uint32_t)n);
+  if (kGrad) p0 = (uint32_t)ld(kCkpt ? a.loc : a.net_off, (uint32_t)n);   // driver pin, or record
   ArcIn ain = arc_input_entry(e0, jl < sl.F, a.rec, a.wire, m, t);
   const ArcBwd v0 = arc_from_input(a, ain, t, load);
   ArcBwd v1{};
@@ -2420,6 +2425,7 @@ __device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int 
   }
   // Single words into the slots (16-byte stores after a transpose over the lanes took as long).
   float* sw = reinterpret_cast<float*>(a.sink);
+  float* rec = reinterpret_cast<float*>(const_cast<float4*>(a.rec));   // checkpointing: spare words of records
   if (kRat) {
     if (v0.valid) *at32(sw, 4 * rat_at((uint32_t)v0.slot) + (uint32_t)(2 * m + v0.tp)) = v0.d;
     if (wide && v1.valid) *at32(sw, 4 * rat_at((uint32_t)v1.slot) + (uint32_t)(2 * m + v1.tp)) = v1.d;
@@ -2452,22 +2458,25 @@ __device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int 
       *at32(sw, aj) = star ? -w : w;
       *at32(sw, aj + 2u) = v.ddx;
     }
-    if (star) *at32(sw, 4 * adj_at(p0) + (uint32_t)t) = v.dsx;
+    if (star) {
+      if (kCkpt) *at32(rec, 4u * (kRecChunks * p0 + 2u + (uint32_t)t) + 3u) = v.dsx;
+      else *at32(sw, 4 * adj_at(p0) + (uint32_t)t) = v.dsx;
+    }
     lu += quad_reduce<kSum>(v.valid ? w * v.ddy : 0.f);
     lv += quad_reduce<kSum>(star ? v.dsy : 0.f);
   };
   arc(v0, jl);
   if (wide) arc(v1, kArcLanes + jl);
   if (jl == 0) {
-    *at32(sw, 4 * rat_at(p0) + (uint32_t)t) = lu;
-    *at32(sw, 4 * rat_at(p0) + 2u + (uint32_t)t) = lv;
+    *(kCkpt ? at32(rec, 4u * (kRecChunks * p0) + 2u + (uint32_t)t) : at32(sw, 4 * rat_at(p0) + (uint32_t)t)) = lu;
+    *(kCkpt ? at32(rec, 4u * (kRecChunks * p0 + 1u) + 2u + (uint32_t)t) : at32(sw, 4 * rat_at(p0) + 2u + (uint32_t)t)) = lv;
   }
 }
 
 // One level l >= 1: workgroups [0, n_chain) the chain role of its nets, the rest the cells of the
 // next lower level (`pre`).  The values that the chain's first loads need come first, preloaded
 // into scalar registers.
-template <bool kSnap, bool kGrad, bool kRat>
+template <bool kSnap, bool kGrad, bool kRat, bool kCkpt>
 __global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0, int e0, int e1, int e2, int e3, int w1,
                                                      int w2, int w3, const int* __restrict__ net_off,
                                                      const int4* __restrict__ ell, BwdArgs a0, Slots sl, Slots pre,
@@ -2482,21 +2491,21 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0
   a.load = snap_bytes<kSnap>(a.load, (size_t)snap_state, sb.s);
   a.sink = snap_bytes<kSnap>(a.sink, a.snap.work, sb.s);
   if (sb.x >= n_chain) {
-    pre_cell<kGrad, kRat>(a, pre, (sb.x - n_chain) * kBlock + (int)threadIdx.x);
+    pre_cell<kGrad, kRat, kCkpt>(a, pre, (sb.x - n_chain) * kBlock + (int)threadIdx.x);
     return;
   }
   const LevelRanges r{nh, h0, e0, e1, e2, e3, r0.e4, r0.e5, w1, w2, w3, r0.w4, r0.w5, r0.g0};
   GroupSlot gs;
   if (!step_slot(sb.x, r, gs)) return;
-  if (gs.block || gs.G == 64) chain_net<64, kGrad, kRat>(a, sl, gs, sh);
-  else if (gs.G == 32) chain_net<32, kGrad, kRat>(a, sl, gs, sh);
-  else if (gs.G == 16) chain_net<16, kGrad, kRat>(a, sl, gs, sh);
-  else if (gs.G == 8) chain_net<8, kGrad, kRat>(a, sl, gs, sh);
-  else chain_net<4, kGrad, kRat>(a, sl, gs, sh);
+  if (gs.block || gs.G == 64) chain_net<64, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 32) chain_net<32, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 16) chain_net<16, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 8) chain_net<8, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else chain_net<4, kGrad, kRat, kCkpt>(a, sl, gs, sh);
 }
 
 // Outputs of every net, after the last level.
-template <bool kGrad, bool kRat>
+template <bool kGrad, bool kRat, bool kCkpt>
 __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int* __restrict__ sched, BwdArgs a,
                                                     int snap_state) {
   __shared__ float sh[kWavesPerBlock * N_ACC];
@@ -2515,26 +2524,27 @@ __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int*
   GroupSlot gs;
   if (!group_slot(range, gs)) return;
   gs.entry = gs.active ? sched[gs.entry] : 0;
-  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat>(a, gs, sh);
-  else if (gs.G == 32) post_net<32, kGrad, kRat>(a, gs, sh);
-  else if (gs.G == 16) post_net<16, kGrad, kRat>(a, gs, sh);
-  else if (gs.G == 8) post_net<8, kGrad, kRat>(a, gs, sh);
-  else post_net<4, kGrad, kRat>(a, gs, sh);
+  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat, kCkpt>(a, gs, sh);
+  else if (gs.G == 32) post_net<32, kGrad, kRat, kCkpt>(a, gs, sh);
+  else if (gs.G == 16) post_net<16, kGrad, kRat, kCkpt>(a, gs, sh);
+  else if (gs.G == 8) post_net<8, kGrad, kRat, kCkpt>(a, gs, sh);
+  else post_net<4, kGrad, kRat, kCkpt>(a, gs, sh);
 }
 
-// Seeds of the endpoints, and beside them the cells role of the deepest level.
-template <bool kGrad, bool kRat>
-__global__ __launch_bounds__(kBlock) void k_bwd_start(EpArgs ea, int n_seed, BwdArgs a, Slots pre, int snap_state) {
+// Seeds of the endpoints list[0..n_ep) (every endpoint when list is NULL), and beside them the cells role of the deepest level.
+template <bool kGrad, bool kRat, bool kCkpt>
+__global__ __launch_bounds__(kBlock) void k_bwd_start(EpArgs ea, const int* __restrict__ list, int n_ep, int n_seed,
+                                                      BwdArgs a, Slots pre, int snap_state) {
   if ((int)blockIdx.x < n_seed) {
     const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
-    if (i < ea.E) ep_seed(ep_snap(ea), i);
+    if (i < n_ep) ep_seed(ep_snap(ea), list ? list[i] : i);
     return;
   }
   a.rec = snap_bytes(a.rec, (size_t)snap_state);
   a.wire = snap_bytes(a.wire, (size_t)snap_state);
   a.load = snap_bytes(a.load, (size_t)snap_state);
   a.sink = snap_bytes(a.sink, a.snap.work);
-  pre_cell<kGrad, kRat>(a, pre, ((int)blockIdx.x - n_seed) * kBlock + (int)threadIdx.x);
+  pre_cell<kGrad, kRat, kCkpt>(a, pre, ((int)blockIdx.x - n_seed) * kBlock + (int)threadIdx.x);
 }
 
 // One backward level's launch, with the kernel compiled for its smallest group, snapshot
@@ -4096,7 +4106,9 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
 //     540 -> 493, 22k 948 -> 1069, 27k 712 -> 795.
 bool split_levels(const sta_graph* g, bool rat) {
   const int64_t per_level = (int64_t)g->n_snap * g->N / std::max(1, g->L);
-  return g->ckpt_stride <= 0 && g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
+  // Checkpointed RC trees keep no list of each segment's nets, for their outputs.
+  if (g->ckpt_stride > 0 && g->rc_ranges.empty()) return false;
+  return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
 }
 
 // Workgroups of the cells role over one level.
@@ -4185,47 +4197,10 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
       default: bwd_launch<6, true>(grid, s, L, canon, grad); break;
     }
   };
-  if (split) {
-    const bool snap = g->n_snap > 1;
-    auto start = [&](auto kern, const Slots& pre) {
-      LaunchTimer t(g, s, STA_K_EP_SEED);
-      const unsigned n_seed = (unsigned)((g->E + kBlock - 1) / kBlock);
-      const unsigned blocks = n_seed + cell_blocks(pre);
-      if (blocks > 0) kern<<<dim3(blocks, g->n_snap), kBlock, 0, s>>>(ea, (int)n_seed, ba, pre, ss);
-    };
-    auto step = [&](auto kern, int l) {
-      const GroupRange& r = g->lvl_ranges[l];
-      const unsigned chain = range_grid(r);
-      const Slots pre = l >= 2 ? level_slots(g, l - 1) : Slots{0, 1, 0, 0};
-      const unsigned blocks = chain + cell_blocks(pre);
-      if (blocks == 0) return;
-      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
-      const int* c = r.cls_off;
-      const int* w = r.wave_off;
-      const LevelRanges lr{c[kNumClasses + 1] - c[kNumClasses], c[kNumClasses], c[0], c[1], c[2], c[3], c[4], c[5],
-                           w[1], w[2], w[3], w[4], w[5], r.g0};
-      kern<<<snap ? level_grid(g, blocks) : dim3(blocks), kBlock, 0, s>>>(
-          (int)chain, lr.nh, lr.h0, lr.e0, lr.e1, lr.e2, lr.e3, lr.w1, lr.w2, lr.w3, d.net_off, d.ell, ba,
-          level_slots(g, l), pre, lr, ss);
-    };
-    auto sweep = [&](auto kstart, auto kstep, auto kout) {
-      start(kstart, level_slots(g, g->L - 1));
-      for (int l = g->L - 1; l >= 1; --l) step(kstep, l);
-      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
-      kout<<<snap_grid(g, range_grid(g->all_range)), kBlock, 0, s>>>(g->all_range, d.sched_all, ba, ss);
-    };
-    if (!grad) snap ? sweep(k_bwd_start<false, true>, k_bwd_step<true, false, true>, k_bwd_out<false, true>)
-                    : sweep(k_bwd_start<false, true>, k_bwd_step<false, false, true>, k_bwd_out<false, true>);
-    else if (rat) snap ? sweep(k_bwd_start<true, true>, k_bwd_step<true, true, true>, k_bwd_out<true, true>)
-                       : sweep(k_bwd_start<true, true>, k_bwd_step<false, true, true>, k_bwd_out<true, true>);
-    else snap ? sweep(k_bwd_start<true, false>, k_bwd_step<true, true, false>, k_bwd_out<true, false>)
-              : sweep(k_bwd_start<true, false>, k_bwd_step<false, true, false>, k_bwd_out<true, false>);
-  } else if (g->ckpt_stride <= 0) {
-    for (int l = g->L - 1; l >= 0; --l) bwd_level(l);
-  } else {
-    // Segments last to first: rebuild the records the forward dropped (the kept ones are
-    // left alone), then that segment's backward levels.  The recomputation needs the
-    // smoothed arrival only where the gradient reads it.
+  // Checkpointing, segments last to first: rebuild the records the forward dropped (the kept ones
+  // are left alone), then `body` with the segment's endpoints and levels.  The recomputation
+  // needs the smoothed arrival only where the gradient reads it.
+  auto segments = [&](auto body) {
     const FwdArgs fa{wire, d.lut_grid, gamma_ps, grad ? 1.0f / gamma_ps : 0.f, 1, 0};
     const RcArgs ra{d.net_off, d.pin_cap, x, y, io, d.sched_all, g->all_range, wire, load, rec, g->N0, g->N,
                     g->cons.r_per_um, g->cons.c_per_um, g->cons.pi_at, g->cons.pi_slew, snap_of(g), nullptr,
@@ -4243,9 +4218,74 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
         fwd_level_launch(g, s, sl, l + 1 < hi ? level_slots(g, l + 1) : Slots{0, 1, 0, 0}, g->n_kept, ss, d.ell, load,
                          d.rec_loc, rec, fa);
       }
-      ep_seed(d.ep_grp + g->ep_grp_off[(size_t)j + 1], g->ep_grp_off[(size_t)j + 2] - g->ep_grp_off[(size_t)j + 1]);
-      for (int l = hi - 1; l >= lo; --l) bwd_level(l);
+      const size_t q = (size_t)j + 1;
+      body(j, d.ep_grp + g->ep_grp_off[q], g->ep_grp_off[q + 1] - g->ep_grp_off[q], lo, hi);
     }
+  };
+  auto sweep_split = [&](auto kstart, auto kstep, auto kout) {
+    const bool snap = g->n_snap > 1;
+    // Levels hi - 1 .. lo: their endpoints' seeds beside the deepest level's cells, then level by level.
+    auto levels = [&](const int* list, int n_ep, int lo, int hi) {
+      const Slots deepest = hi > lo ? level_slots(g, hi - 1) : Slots{0, 1, 0, 0};
+      const unsigned n_seed = (unsigned)((n_ep + kBlock - 1) / kBlock), blocks = n_seed + cell_blocks(deepest);
+      if (blocks > 0) {
+        LaunchTimer t(g, s, STA_K_EP_SEED);
+        kstart<<<dim3(blocks, g->n_snap), kBlock, 0, s>>>(ea, list, n_ep, (int)n_seed, ba, deepest, ss);
+      }
+      for (int l = hi - 1; l >= lo; --l) {
+        const GroupRange& r = g->lvl_ranges[l];
+        const unsigned chain = range_grid(r);
+        const Slots pre = l > lo ? level_slots(g, l - 1) : Slots{0, 1, 0, 0};
+        const unsigned all = chain + cell_blocks(pre);
+        if (all == 0) continue;
+        LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+        const int* c = r.cls_off;
+        const int* w = r.wave_off;
+        const LevelRanges lr{c[kNumClasses + 1] - c[kNumClasses], c[kNumClasses], c[0], c[1], c[2], c[3], c[4], c[5],
+                             w[1], w[2], w[3], w[4], w[5], r.g0};
+        kstep<<<snap ? level_grid(g, all) : dim3(all), kBlock, 0, s>>>(
+            (int)chain, lr.nh, lr.h0, lr.e0, lr.e1, lr.e2, lr.e3, lr.w1, lr.w2, lr.w3, d.net_off, d.ell, ba,
+            level_slots(g, l), pre, lr, ss);
+      }
+    };
+    auto outputs = [&](const GroupRange& r) {
+      const unsigned blocks = range_grid(r);
+      if (blocks == 0) return;
+      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+      kout<<<snap_grid(g, blocks), kBlock, 0, s>>>(r, d.sched_all, ba, ss);
+    };
+    if (g->ckpt_stride <= 0) {
+      levels(nullptr, g->E, 1, g->L);
+      outputs(g->all_range);
+      return;
+    }
+    // Nets whose sinks hold segment slots give their outputs with their segment, the others (level 0
+    // among them; their records are kept too) at the end: the lists of the RC passes.
+    segments([&](int j, const int* list, int n_ep, int lo, int hi) {
+      levels(list, n_ep, lo, hi);
+      outputs(g->rc_ranges[(size_t)j + 1]);
+    });
+    outputs(g->rc_ranges[0]);
+  };
+  auto sweep = [&](auto snap, auto ckpt) {
+    constexpr bool S = decltype(snap)::value, K = decltype(ckpt)::value;
+    if (!grad) sweep_split(k_bwd_start<false, true, K>, k_bwd_step<S, false, true, K>, k_bwd_out<false, true, K>);
+    else if (rat) sweep_split(k_bwd_start<true, true, K>, k_bwd_step<S, true, true, K>, k_bwd_out<true, true, K>);
+    else sweep_split(k_bwd_start<true, false, K>, k_bwd_step<S, true, false, K>, k_bwd_out<true, false, K>);
+  };
+  if (split) {
+    const bool ckpt = g->ckpt_stride > 0, snap = g->n_snap > 1;
+    using T = std::true_type;
+    using F = std::false_type;
+    if (ckpt) snap ? sweep(T{}, T{}) : sweep(F{}, T{});
+    else snap ? sweep(T{}, F{}) : sweep(F{}, F{});
+  } else if (g->ckpt_stride <= 0) {
+    for (int l = g->L - 1; l >= 0; --l) bwd_level(l);
+  } else {
+    segments([&](int, const int* list, int n, int lo, int hi) {
+      ep_seed(list, n);
+      for (int l = hi - 1; l >= lo; --l) bwd_level(l);
+    });
     bwd_level(0);
   }
   if (grad && tree && (out->dx || out->dy)) {

@@ -1,5 +1,5 @@
-"""Backward sweep split by role against the fused level kernel, its passes without required times or
-without the gradient, and RC-tree chunks at the edges of their packing."""
+"""Backward sweep split by role: under checkpointing, against the fused level kernel, its passes without
+required times or without the gradient; and RC-tree chunks at the edges of their packing."""
 from __future__ import annotations
 
 import numpy as np
@@ -26,9 +26,9 @@ def _sweep(g, x, y, wns=False, pins=True, **kind):
 
 @pytest.mark.parametrize("design", ["tail", "wide", "fanout"])
 @pytest.mark.parametrize("kind", range(3))
-def test_split_levels_equal_fused_bitwise(design, kind):
-    # Checkpointing in one segment runs the fused kernel over the same records: heavy-tailed nets
-    # (every class and whole workgroups), cells of 5-8 inputs, a net of over 512 sinks.
+def test_split_levels_under_checkpointing_equal_plain_bitwise(design, kind):
+    # One segment (every slot shared), several, and one per level: heavy-tailed nets (every class and
+    # whole workgroups), cells of 5-8 inputs, a net of over 512 sinks.
     d = {"tail": lambda: make_design(scaled_spec(30_000, cfg_id=81, box_um=400.0)),
          "wide": lambda: wide_dag(n_levels=9, gates_per_level=70, n_pi=16, seed=5),
          "fanout": lambda: fanout_design(via_cell=True)}[design]()
@@ -36,12 +36,13 @@ def test_split_levels_equal_fused_bitwise(design, kind):
     g.levelize()
     x, y = torch.tensor(d.x, device="cuda"), torch.tensor(d.y, device="cuda")
     print(f"roles: {design} {KINDS[kind]}", flush=True)
-    split = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
-    g.set_checkpointing(1000)
-    fused = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
-    assert set(split) == set(fused)
-    for k in split:
-        assert np.array_equal(split[k], fused[k], equal_nan=True), k
+    plain = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
+    for stride in (1000, 3, 1):
+        g.set_checkpointing(stride)
+        got = _sweep(g, x, y, wns=kind == 1, **KINDS[kind])
+        assert set(got) == set(plain)
+        for k in plain:
+            assert np.array_equal(got[k], plain[k], equal_nan=True), (stride, k)
 
 
 @pytest.mark.parametrize("kind,S", [(0, 24), (1, 40), (2, 24)])
