@@ -20,7 +20,7 @@ constexpr int kLutKeysAt = kLutCells;      // in the tables' device array: the b
 constexpr int kLutCoefAt = kLutCells + 3;  // three float4) follow the grid, then the coefficients
 constexpr int kFlatG0Default = 2;    // flat kernels (RC, outputs): smallest group 4 lanes
 constexpr int kSweepG0Default = 2;   // level kernels: smallest backward group 4 lanes (one per condition)
-constexpr int kTreeChunk = 1024;     // RC trees: pins of whole nets swept by one workgroup in LDS
+constexpr int kTreeChunk = 1024;     // RC trees: most pins of whole nets swept by one workgroup in LDS
 constexpr int kSiHeavy = 12;         // snapshot-inner layout: nets with more sinks take a whole
                                      // workgroup for up to 64 snapshots,
 constexpr int kSiHuge = 128;         // nets with more than this a workgroup per 8 snapshots (RC,
@@ -70,8 +70,10 @@ struct StateLayout {
 
 struct WorkLayout {
   size_t sink;     // float4[2 * P]: per sink its required time by condition, then its adjoint
-                   // {a_rise, a_fall, s_rise, s_fall}; interleaved, so that the scattered
-                   // writes of one sink fill one aligned 32-byte segment
+                   // {a_rise, a_fall, s_rise / slew, s_fall / slew}; interleaved, so that the
+                   // scattered writes of one sink fill one aligned 32-byte segment.  Before its
+                   // cell step a sink's slot, and always a driver pin's, may hold what the
+                   // split backward prepared (k_bwd_step)
   size_t tree_adj; // RC trees only, float2[P]: adjoints of each sink's {Delay, Impulse} and
                    // of each net's root load (at its driver), from the backward sweep
   size_t tree_bar; // RC trees only, float4[2 * P]: adjoint scratch of the tree passes

@@ -22,7 +22,9 @@
 //    256-thread workgroup for nets over 64 sinks; reductions over a net's sinks are DPP
 //    and xor butterflies inside the group, across waves through LDS in a fixed order
 //    (no atomics, Sec. 3.1.1).
-//  * The one-pass RC kernel and the forward output expansion use groups from 4 lanes.
+//  * The one-pass RC kernel and the output passes use groups from 4 lanes.
+// The backward level runs these steps side by side on workgroups of their own (k_bwd_step) with
+// per-pin outputs in one pass at the end; wide levels run them fused (k_bwd_level).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -2116,19 +2118,22 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level(int nh, int h0, int e0, in
 }
 
 // ---------------------------------------------------------------------------- backward, split by role
-// The backward level in three roles that run side by side in one launch, on workgroups of
-// their own, instead of one after the other in the lanes of a net (k_bwd_level):
+// The backward sweep in three roles, on workgroups of their own instead of one after the other in
+// the lanes of a net (k_bwd_level); a level's launch runs the first two side by side:
 //  * cells (pre): for the cells of the next lower level, everything of the cell step that the
 //    forward state alone decides - per input the arc delays, softmax weights and table
 //    partials - written into the inputs' own workspace slots, which are empty until the cell
 //    step fills them;
 //  * chain: the net step's reductions and the cell step as one multiply-add per input, in
 //    place in those slots: the only part that the next level waits for;
-//  * outputs (post): per-pin outputs and the Elmore adjoint, from the same sinks.
+//  * outputs (post): per-pin outputs and the Elmore adjoint, from the same sinks, in one pass
+//    after the last level.
 // A level of one design holds about one wave per SIMD, so that its time is the instruction
 // chain and the dependent loads of one wave, not bytes: in one wave the lookups (three round
-// trips), reductions and outputs of a 2.5M-pin level took 5.9 us; apart, the longest role
-// bounds the launch.
+// trips), reductions and outputs took 6.1 us a level at 2.6M pins and 5.5 at 68k.  The roles timed
+// by themselves: chain 4.3 and 3.5 us, cells 3.9 and 3.1, chain and cells together 5.2 and 3.7,
+// outputs 4.9 and 5.4 a level (their reductions, then stores that the kernel's end waits
+// for), but 84 and 9 us for all levels in one pass.
 //
 // What a slot holds before and after the cell step of the cell it feeds (k' = input condition,
 // i = input transition, t the output transition that the arc's unateness pairs with it):
@@ -2300,8 +2305,8 @@ __device__ __forceinline__ void chain_net(const BwdArgs& a, const Slots& sl, con
 // Outputs role of one net: the net step again, for its per-pin outputs, and the Elmore adjoint.
 // Bound by memory: 2.6M pins in canonical order with every output take 84 us with plain stores (368
 // MB, 4.4 TB/s; a 4 GiB copy reaches 4.8), 103 us with streaming ones, which leave L2 before a
-// line's pieces - its sinks' and its drivers' - have met there.
-template <int G, bool kGrad, bool kRat, bool kCkpt>
+// line's pieces - its sinks' and its drivers' - have met there; kStream: see stream_outputs.
+template <int G, bool kGrad, bool kRat, bool kCkpt, bool kStream>
 __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, float* sh) {
   const int gl = gs.gl;
   const bool block = gs.block;
@@ -2334,7 +2339,9 @@ __device__ __forceinline__ void post_net(const BwdArgs& a, const GroupSlot& gs, 
   SinkIn in1{};
   if (block) in1 = load(has1 ? s0 + stride : p0);
   auto put = [&](float4* out, uint32_t q, const float4& v) {
-    if (out) *at32(out, q) = v;
+    if (!out) return;
+    if (kStream) store_stream(at32(out, q), v);
+    else *at32(out, q) = v;
   };
   auto arrive = [&](uint32_t q, const float4& at, const float4& sl) {
     put(a.at_out, q, at);
@@ -2505,7 +2512,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0
 }
 
 // Outputs of every net, after the last level.
-template <bool kGrad, bool kRat, bool kCkpt>
+template <bool kGrad, bool kRat, bool kCkpt, bool kStream>
 __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int* __restrict__ sched, BwdArgs a,
                                                     int snap_state) {
   __shared__ float sh[kWavesPerBlock * N_ACC];
@@ -2524,11 +2531,11 @@ __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int*
   GroupSlot gs;
   if (!group_slot(range, gs)) return;
   gs.entry = gs.active ? sched[gs.entry] : 0;
-  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat, kCkpt>(a, gs, sh);
-  else if (gs.G == 32) post_net<32, kGrad, kRat, kCkpt>(a, gs, sh);
-  else if (gs.G == 16) post_net<16, kGrad, kRat, kCkpt>(a, gs, sh);
-  else if (gs.G == 8) post_net<8, kGrad, kRat, kCkpt>(a, gs, sh);
-  else post_net<4, kGrad, kRat, kCkpt>(a, gs, sh);
+  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 32) post_net<32, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 16) post_net<16, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 8) post_net<8, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else post_net<4, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
 }
 
 // Seeds of the endpoints list[0..n_ep) (every endpoint when list is NULL), and beside them the cells role of the deepest level.
@@ -4111,6 +4118,17 @@ bool split_levels(const sta_graph* g, bool rat) {
   return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
 }
 
+// Whether k_bwd_out writes its outputs as streaming stores.  Those are the slower ones (see post_net),
+// but leave the 256 MB last-level cache to the state and graph that the next call reads: worth it
+// once the outputs fill most of that cache, in canonical order, where stores cover whole lines.
+// A step repeated on one placement, plain and streaming: 2.6M pins (187 MB) 883 and 838 us; 108k pins in 8
+// snapshots (62 MB) 302 and 310; 637k pins (46 MB) 312 and 317; 414k pins with RC trees in original order 400
+// and 428.
+bool stream_outputs(const sta_graph* g, const int* io, const sta_bwd_out& out) {
+  const int64_t bytes = (int64_t)g->n_snap * g->P * 16 * (!!out.at + !!out.slew + !!out.rat + !!out.slack);
+  return io == nullptr && bytes > (128ll << 20);
+}
+
 // Workgroups of the cells role over one level.
 unsigned cell_blocks(const Slots& sl) {
   return (unsigned)(((size_t)kCellLanes * sl.nc + kBlock - 1) / kBlock);
@@ -4269,9 +4287,13 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
   };
   auto sweep = [&](auto snap, auto ckpt) {
     constexpr bool S = decltype(snap)::value, K = decltype(ckpt)::value;
-    if (!grad) sweep_split(k_bwd_start<false, true, K>, k_bwd_step<S, false, true, K>, k_bwd_out<false, true, K>);
-    else if (rat) sweep_split(k_bwd_start<true, true, K>, k_bwd_step<S, true, true, K>, k_bwd_out<true, true, K>);
-    else sweep_split(k_bwd_start<true, false, K>, k_bwd_step<S, true, false, K>, k_bwd_out<true, false, K>);
+    const bool stream = stream_outputs(g, io, *out);
+    if (!grad) sweep_split(k_bwd_start<false, true, K>, k_bwd_step<S, false, true, K>,
+                           stream ? k_bwd_out<false, true, K, true> : k_bwd_out<false, true, K, false>);
+    else if (rat) sweep_split(k_bwd_start<true, true, K>, k_bwd_step<S, true, true, K>,
+                              stream ? k_bwd_out<true, true, K, true> : k_bwd_out<true, true, K, false>);
+    else sweep_split(k_bwd_start<true, false, K>, k_bwd_step<S, true, false, K>,
+                     stream ? k_bwd_out<true, false, K, true> : k_bwd_out<true, false, K, false>);
   };
   if (split) {
     const bool ckpt = g->ckpt_stride > 0, snap = g->n_snap > 1;
