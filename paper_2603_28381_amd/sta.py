@@ -214,6 +214,8 @@ def _stream_handle(stream=None) -> int | None:
 
 
 def _dev_f32(a, device) -> torch.Tensor:
+    if isinstance(a, torch.Tensor) and a.dtype == torch.float32 and a.device == device and a.is_contiguous():
+        return a
     t = torch.as_tensor(a)
     if t.dtype != torch.float32 or t.device != torch.device(device) or not t.is_contiguous():
         t = t.to(device=device, dtype=torch.float32).contiguous()
@@ -316,9 +318,16 @@ class Graph:
         _check(_lib.sta_levelize(self._h, ctypes.byref(n)))
         return n.value
 
-    def info(self) -> dict:
+    def _info(self) -> StaGraphInfo:
+        # The calls of a sweep read one or two fields: 0.7 us, the dict of all of them 2.1.  Small
+        # designs are bound by the host's time per call (an autograd step of 841k pins, four such
+        # reads and the tensors' checks: 568 -> 555 us).
         i = StaGraphInfo()
         _check(_lib.sta_graph_info_get(self._h, ctypes.byref(i)))
+        return i
+
+    def info(self) -> dict:
+        i = self._info()
         return {k: getattr(i, k) for k, _ in StaGraphInfo._fields_}
 
     def levelization(self) -> dict:
@@ -415,10 +424,10 @@ class Graph:
 
     # ------------------------------------------------------------------ sweeps
     def new_state(self, device="cuda") -> torch.Tensor:
-        return torch.empty(self.info()["fwd_state_bytes"], dtype=torch.uint8, device=device)
+        return torch.empty(self._info().fwd_state_bytes, dtype=torch.uint8, device=device)
 
     def new_workspace(self, device="cuda") -> torch.Tensor:
-        return torch.empty(self.info()["bwd_workspace_bytes"], dtype=torch.uint8, device=device)
+        return torch.empty(self._info().bwd_workspace_bytes, dtype=torch.uint8, device=device)
 
     def forward(self, x, y, gamma: float = 10.0, smooth: bool = True, canonical: bool = False,
                 pins: bool = False, state: torch.Tensor | None = None, scalars: torch.Tensor | None = None,
@@ -426,8 +435,8 @@ class Graph:
         dev = x.device if isinstance(x, torch.Tensor) and x.is_cuda else torch.device("cuda")
         x = _dev_f32(x, dev)
         y = _dev_f32(y, dev)
-        inf = self.info()
-        S, nd = inf["n_snapshots"], inf["n_designs"]
+        inf = self._info()
+        S, nd = inf.n_snapshots, inf.n_designs
         lead = (S,) if S > 1 else ()
         state = self.new_state(dev) if state is None else state
         if scalars is None:
@@ -455,7 +464,7 @@ class Graph:
         dev = fwd.state.device
         x = _dev_f32(x, dev)
         y = _dev_f32(y, dev)
-        S = self.info()["n_snapshots"]
+        S = self._info().n_snapshots
         if noalloc and (workspace is not None or capture):
             raise ValueError("noalloc takes neither a workspace nor capture")
         ws = None if noalloc else (self.new_workspace(dev) if workspace is None else workspace)
