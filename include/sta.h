@@ -223,7 +223,8 @@ sta_status sta_forward(sta_graph* g, const float* x, const float* y, sta_fwd_out
  * Errors: STA_E_STATE (not levelized / not uploaded; a state that the latest of this graph's
  * sta_forward calls into it computed under a schedule of the other kernel family; with
  * STA_GRAD also a state that call did not compute with STA_SMOOTH and the same gamma_ps, or
- * that no sta_forward on this graph produced), STA_E_INVALID.
+ * that no sta_forward on this graph produced), STA_E_INVALID (also when the workspace of one
+ * snapshot, 32 bytes a pin or a checkpointing slot, would reach 4 GiB).
  * ------------------------------------------------------------------------------------- */
 sta_status sta_backward(sta_graph* g, const float* x, const float* y, const sta_fwd_out* fwd,
                         sta_bwd_out* out, uint32_t flags, float gamma_ps, sta_stream stream);

@@ -2614,6 +2614,17 @@ sta_status check_ready(sta_graph* g) {
   return STA_OK;
 }
 
+// The backward kernels reach the sink workspace, 32 bytes a slot, through 32-bit byte offsets
+// from a snapshot's base.  That array is wider than those checked at levelization, and a
+// forward sweep has none.
+sta_status check_backward_size(const sta_graph* g) {
+  if (!g) return fail(STA_E_INVALID, "graph is NULL");
+  if (!g->levelized) return fail(STA_E_STATE, "graph is not levelized");
+  if (2 * sizeof(float4) * (uint64_t)(g->n_sslots > 0 ? g->n_sslots : g->P) >= 1ull << 32)
+    return fail(STA_E_INVALID, "graph too large for a backward sweep: the sink workspace of one snapshot reaches 4 GiB");
+  return STA_OK;
+}
+
 // Launch timing while profiling is on (sta_profile_enable).  Consecutive launches of one
 // kind form a run bracketed by one event pair, so that no event sits between two dependent
 // launches of a level loop: the per-launch average is then the kernels' own back-to-back
@@ -4446,7 +4457,8 @@ extern "C" sta_status sta_forward(sta_graph* g, const float* x, const float* y, 
 
 extern "C" sta_status sta_backward(sta_graph* g, const float* x, const float* y, const sta_fwd_out* fwd,
                                    sta_bwd_out* out, uint32_t flags, float gamma_ps, sta_stream stream) {
-  sta_status st = check_ready(g);
+  sta_status st = check_backward_size(g);
+  if (st == STA_OK) st = check_ready(g);
   if (st != STA_OK) return st;
   if (!fwd || !fwd->state || !out || !out->workspace) return fail(STA_E_INVALID, "state and workspace are required");
   const bool grad = (flags & STA_GRAD) != 0;
@@ -4562,7 +4574,8 @@ extern "C" sta_status sta_tune_cached(sta_graph* g, sta_schedule* sch) {
 
 extern "C" sta_status sta_tune(sta_graph* g, const float* x, const float* y, float gamma_ps, int32_t reps,
                                sta_schedule* best, sta_stream stream) {
-  sta_status st = check_ready(g);
+  sta_status st = check_backward_size(g);
+  if (st == STA_OK) st = check_ready(g);
   if (st != STA_OK) return st;
   if (!x || !y) return fail(STA_E_INVALID, "x and y are required");
   if (!(gamma_ps > 0.f && std::isfinite(gamma_ps))) return fail(STA_E_INVALID, "gamma must be positive");

@@ -434,3 +434,31 @@ def test_rc_tree_batch_with_star_member_levelizes():
     g.levelize()
     assert g.info()["n_designs"] == 2
     g.close()
+
+
+@pytest.mark.slow
+def test_backward_refuses_a_sink_workspace_of_4_gib():
+    # One net of 2^27 pins: 32 bytes a pin are 4 GiB, which 32-bit byte offsets do not reach; with
+    # checkpointing its 2^27 - 1 sinks have the slots, 32 bytes below.
+    P = 1 << 27
+    kind = np.full(P, PIN_PO, np.int8)
+    kind[0] = PIN_PI
+    lib = make_design(tiny_spec(8, 2, n_pi=2, seed=1)).lib
+    g = S.Graph(dict(n_pins=P, n_nets=1, n_cells=0, net_offsets=[0, P], net_pins=np.arange(P, dtype=np.int32),
+                     cell_type=[], cell_in_offsets=[0], cell_in_pins=[], cell_out_pin=[],
+                     pin_cap=np.zeros(P, np.float32), pin_kind=kind),
+                dict(n_cell_types=lib.n_cell_types, arc_offsets=lib.arc_offsets, arc_unate=lib.arc_unate,
+                     slew_axis=lib.slew_axis, load_axis=lib.load_axis, tables=lib.tables),
+                dict(t_clk=100.0, setup=5.0, hold=2.0, pi_at=0.0, pi_slew=10.0, r_per_um=0.1, c_per_um=0.2))
+    g.levelize()
+    assert g.info()["bwd_workspace_bytes"] == 1 << 32
+
+    def backward():                                  # no buffers: refused before they matter
+        return S.load_library().sta_backward(g.handle, None, None, None, None, 0, 10.0, None), \
+            S.load_library().sta_last_error().decode()
+
+    code, why = backward()
+    assert code == S.STA_E_INVALID and "4 GiB" in why
+    g.set_checkpointing(1)
+    assert "4 GiB" not in backward()[1]
+    g.close()
