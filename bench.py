@@ -48,6 +48,12 @@ def algorithmic_bytes(d, level: np.ndarray, n_levels: int | None = None, snapsho
                  per cell input 9 + 64 (wire, source slew and smoothed AT, seed writes); per
                  sink 4 (cap) + 48 (RAT, adjoint, wire, x, y); per pin 72 output writes (AT,
                  slew, RAT, slack, dx, dy)
+    and, where the per-pin outputs follow the levels in a pass of their own, instead of bwd_level
+      bwd_step   (levels L-1..1; the deepest level's lookups run in the seeds' launch) per net 8
+                 (offset) + 8 (late slews); per cell and cell input as above; per sink 36 (RAT,
+                 adjoint, wire delay)
+      bwd_out    per net 8 (sched, offset) + 40 (record, driver x, y); per cell 16 (load
+                 partials); per sink 4 (cap) + 48; per pin 72 output writes
     """
     S = int(snapshots)
     N, P = d.n_nets, d.n_pins
@@ -75,6 +81,10 @@ def algorithmic_bytes(d, level: np.ndarray, n_levels: int | None = None, snapsho
     out["bwd_level"] = np.array([float(nets_l[l] * (8 + 40 * S) + cells_l[l] * (12 + 4 * S) + ins_l[l] * (9 + 64 * S)
                                        + sinks_l[l] * (4 + 48 * S) + pins_l[l] * 72 * S)
                                  for l in range(L - 1, -1, -1)])
+    out["bwd_step"] = np.array([float(nets_l[l] * (8 + 8 * S) + cells_l[l] * (12 + 4 * S) + ins_l[l] * (9 + 64 * S)
+                                      + sinks_l[l] * 36 * S) for l in range(L - 1, 0, -1)])
+    out["bwd_out"] = np.array([float(N * (8 + 40 * S) + cells_l.sum() * 16 * S + sinks.sum() * (4 + 48 * S)
+                                     + P * 72 * S)])
     return out
 
 
@@ -97,20 +107,15 @@ def whole_sweep_bytes(d) -> dict:
 
 
 def whole_sweep_roofline(d, kernels: dict, ms_step: float) -> dict:
-    """Fractions of HBM peak under whole_sweep_bytes: the backward level kernel (the whole backward
-    sweep's bytes over its summed launch time), the forward sweep (RC, levels, endpoint
-    scalars) and the whole step."""
+    """Fractions of HBM peak under whole_sweep_bytes: the forward sweep (RC, levels, endpoint
+    scalars), the backward sweep (seeds, levels, outputs) and the whole step."""
     b = whole_sweep_bytes(d)
-    fwd_ms = sum(kernels[k]["ms_per_step"] for k in ("rc", "fwd_level", "ep_partial", "ep_final") if k in kernels)
-    bl = kernels["bwd_level"]
+    ms = lambda *ks: sum(kernels[k]["ms_per_step"] for k in ks if k in kernels)  # noqa: E731
     out = {"model": "whole_sweep_bytes (whole-sweep byte model per pin)",
-           "bwd_level": {"bytes_per_launch": round(b["backward"] / bl["launches_per_step"], 1),
-                         "avg_launch_us": round(bl["avg_us"], 3)},
-           "forward_sweep": {"bytes": b["forward"], "ms": round(fwd_ms, 4)},
+           "forward_sweep": {"bytes": b["forward"], "ms": round(ms("rc", "fwd_level", "ep_partial", "ep_final"), 4)},
+           "backward_sweep": {"bytes": b["backward"], "ms": round(ms("ep_seed", "bwd_level", "expand"), 4)},
            "step": {"bytes": b["forward"] + b["backward"], "ms": round(ms_step, 4)}}
-    gbs = b["backward"] / (bl["ms_per_step"] * 1e-3) / 1e9
-    out["bwd_level"].update(achieved_gbs=round(gbs, 2), frac=round(gbs / HBM_PEAK_GBS, 5))
-    for k in ("forward_sweep", "step"):
+    for k in ("forward_sweep", "backward_sweep", "step"):
         gb = out[k]["bytes"] / (out[k]["ms"] * 1e-3) / 1e9
         out[k].update(achieved_gbs=round(gb, 2), frac=round(gb / HBM_PEAK_GBS, 5))
     return out
@@ -178,8 +183,17 @@ def counted_traffic(kernel: str, summary: str = "sta_sweep_2p5Mpins_hbm_counters
     return None
 
 
+def lanes_traffic(family: str) -> float | None:
+    """counted_traffic of a backward kernel family in the snapshot-lane kernels."""
+    kernel = {"bwd_level": "k_bwd_level_si", "expand": "k_bwd_out_si"}.get(family)
+    return kernel and counted_traffic(kernel, "sta_snapshot_lanes_64snap_kernel_stats.md")
+
+
 def kernel_table(prof: dict, alg: dict, steps: int) -> tuple[dict, dict]:
-    """Per-kernel launch statistics and the roofline entry of the dominant kernel."""
+    """Per-kernel launch statistics and the roofline entry of the dominant kernel.  The steps profiled
+    here take no per-pin outputs from the forward, so `expand` is the backward's output pass."""
+    if prof["expand"][0] > 0:
+        alg = dict(alg, bwd_level=alg["bwd_step"], expand=alg["bwd_out"])
     kernels = {}
     for k, (n, tot) in prof.items():
         if n == 0:
@@ -371,8 +385,7 @@ def run_batch(args) -> dict:
         alg = algorithmic_bytes(d1, g1.levelization()["level"], snapshots=64)
         kernels, roofline = kernel_table(prof, alg, args.steps)
         roofline["scope"] = "the 64-snapshot graph's launches"
-        roofline["traffic"] = (counted_traffic("k_bwd_level_si", "sta_snapshot_lanes_64snap_kernel_stats.md")
-                               if inner and roofline["kernel"] == "bwd_level" else None)
+        roofline["traffic"] = lanes_traffic(roofline["kernel"]) if inner else None
 
     cpu = None
     if not args.no_cpu_baseline and not getattr(args, "lean", False):
@@ -437,9 +450,7 @@ def snapshot_graph_only(args, g1, d1, x1, y1, dev, best1, t_setup) -> dict:
         alg = algorithmic_bytes(d1, g1.levelization()["level"], snapshots=64)
         kernels, roofline = kernel_table(prof, alg, args.steps)
         roofline["scope"] = "the 64-snapshot graph's launches"
-        roofline["traffic"] = (counted_traffic("k_bwd_level_si", "sta_snapshot_lanes_64snap_kernel_stats.md")
-                               if args.snapshot_layout == "inner" and roofline["kernel"] == "bwd_level"
-                               else None)
+        roofline["traffic"] = lanes_traffic(roofline["kernel"]) if args.snapshot_layout == "inner" else None
     P = 64 * d1.n_pins
     return {
         "metric": "STA fwd+bwd pins/sec, 64 placement snapshots in one sweep",
@@ -502,7 +513,8 @@ def run_single(args) -> dict:
         g.profile(False)
         kernels, roofline = kernel_table(prof, algorithmic_bytes(d, lev["level"]), args.steps)
         if args.workload == "cfg2" and not args.trees and args.fwd_cell_lanes == 16 and args.sweep_group_log2 == 2:
-            roofline["traffic"] = counted_traffic("k_" + roofline["kernel"])
+            name = {"bwd_level": "bwd_step" if "expand" in kernels else "bwd_level", "expand": "bwd_out"}
+            roofline["traffic"] = counted_traffic("k_" + name.get(roofline["kernel"], roofline["kernel"]))
         # The per-launch floor of this machine for comparison: back-to-back dependent launches of
         # a trivial elementwise kernel over as many threads as a level launch has.
         roofline["launch_floor_us"] = round(launch_floor_us(dev, 256 * 450), 2)
@@ -716,6 +728,7 @@ def run_rc(args) -> dict:
             r[scheme] = {"rc_us": round(us, 2), "rc_gbs": round(r["rc_alg_bytes"] / (us * 1e-6) / 1e9, 1),
                          "fwd_level_us": round(1e3 * prof["fwd_level"][1] / max(1, prof["fwd_level"][0]), 2),
                          "bwd_level_us": round(1e3 * prof["bwd_level"][1] / max(1, prof["bwd_level"][0]), 2),
+                         "bwd_out_us": round(1e3 * prof["expand"][1] / max(1, prof["expand"][0]), 2),
                          "step_ms": round(ms, 4)}
         g.set_schedule(2, 2, 64, "groups", 16, "groups")
         r["groups_speedup_vs_thread"] = round(r["thread"]["rc_us"] / r["groups"]["rc_us"], 2)

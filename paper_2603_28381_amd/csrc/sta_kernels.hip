@@ -3990,7 +3990,7 @@ sta_status launch_backward_si(sta_graph* g, const float* x, const float* y, cons
       LaunchTimer t(g, s, STA_K_BWD_LEVEL);
       level<<<dim3(blocks, D.gy), kb, 0, s>>>(lo, hs, us, hi, level_slots(g, l), ba);
     }
-    LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+    LaunchTimer t(g, s, STA_K_EXPAND);
     outputs<<<dim3((unsigned)(nh * D.hch + nu * D.uch) + si_blocks(g->N, D.sl2, kSiRcBlock / 64), D.gy), kSiRcBlock, 0,
               s>>>(oa);
   };
@@ -4280,7 +4280,7 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
     auto outputs = [&](const GroupRange& r) {
       const unsigned blocks = range_grid(r);
       if (blocks == 0) return;
-      LaunchTimer t(g, s, STA_K_BWD_LEVEL);
+      LaunchTimer t(g, s, STA_K_EXPAND);
       kout<<<snap_grid(g, blocks), kBlock, 0, s>>>(r, d.sched_all, ba, ss);
     };
     if (g->ckpt_stride <= 0) {

@@ -99,3 +99,26 @@ def test_tree_chunk_packing_edges(pins):
     ref = O.run(d, gamma=GAMMA, grad="tns")
     check_values(d, got, ref)
     check_grad(got, ref, 1e-3, 1e-6)
+
+
+@pytest.mark.parametrize("form", ["split", "lanes", "fused"])
+def test_profile_counts_levels_apart_from_the_output_pass(form):
+    # Split levels and snapshot lanes: a launch a level above 0, then one output pass of all nets.  The
+    # fused kernel (past the nets a level of the split rule): a launch a level, outputs within.
+    d = make_design(scaled_spec(60_000, cfg_id=82, box_um=500.0))
+    g = Graph.from_design(d)
+    L = g.levelize()
+    S = {"split": 1, "lanes": 2, "fused": 24}[form]
+    if S > 1:
+        g.set_snapshots(S)
+    if form == "lanes":
+        g.set_snapshot_layout(True)
+    x, y = (torch.tensor(np.repeat(v[None], S, 0) if S > 1 else v, device="cuda") for v in (d.x, d.y))
+    if form == "lanes":
+        x, y = x.t().contiguous(), y.t().contiguous()
+    g.profile(True)
+    _sweep(g, x, y, **KINDS[0])
+    got = g.profile_read()
+    g.profile(False)
+    assert got["fwd_level"][0] == L - 1 and got["ep_seed"][0] == 1
+    assert (got["bwd_level"][0], got["expand"][0]) == ((L, 0) if form == "fused" else (L - 1, 1))
