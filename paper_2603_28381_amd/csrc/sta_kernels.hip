@@ -1169,12 +1169,12 @@ __global__ __launch_bounds__(kBlock) void k_fwd_level(int nc, int n0, int base, 
   a.wire = snap_bytes<kSnap>(a.wire, (size_t)snap_state, sb.s);
   const int gid = sb.x * kBlock + (int)threadIdx.x;
   const int kc = gid / kCellLanes;
-  if (!kSnap && a.next_nc > 0) {
-    const int b = sb.x - prefetch_block(nc);
-    if (b >= 0) {
-      fwd_prefetch(ell, loads, base + F * nc, a.next_F, a.next_nc, n0 + nc, b);
-      return;
-    }
+  // Only a grid with prefetching workgroups reaches past this level's own.  No argument but the
+  // preloaded ones is looked at before the first loads: a wait for next_nc here took 0.2-0.4 us a
+  // level (2.88 -> 2.67 at 63k pins, 3.80 -> 3.40 at 3.5M, where nothing is prefetched).
+  if (!kSnap && sb.x >= prefetch_block(nc)) {
+    fwd_prefetch(ell, loads, base + F * nc, a.next_F, a.next_nc, n0 + nc, sb.x - prefetch_block(nc));
+    return;
   }
   if (kc >= sl.nc) return;                     // uniform over the cell's 16 lanes
   const LutKeys keys = lut_keys_at(a.lut);
