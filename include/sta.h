@@ -505,7 +505,8 @@ sta_status sta_server_set_max_merge(sta_server* s, int32_t max_merge);
 #define STA_K_EXPAND 4       /* per-pin outputs: of the forward, and of the backward where a pass of
                                 its own writes them after the levels */
 #define STA_K_EP_SEED 5      /* backward seeds (with the deepest level's lookups where levels are split) */
-#define STA_K_BWD_LEVEL 6    /* one backward level (RAT, slack, adjoint) */
+#define STA_K_BWD_LEVEL 6    /* one backward level (RAT, slack, adjoint); under checkpointing the lowest
+                                of a segment may write that segment's outputs too */
 #define STA_K_RECOMPUTE 7    /* one forward level recomputed from a checkpoint */
 #define STA_K_RC_ADJOINT 8   /* Elmore adjoint through RC trees (graphs with pin_parent) */
 #define STA_K_COUNT 9

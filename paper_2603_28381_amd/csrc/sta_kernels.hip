@@ -309,18 +309,18 @@ struct GroupSlot {
   bool block;   // a whole workgroup serves one net
 };
 
-__device__ __forceinline__ bool group_slot(const GroupRange& r, GroupSlot& s) {
+__device__ __forceinline__ bool group_slot(const GroupRange& r, GroupSlot& s, int bx) {
   const int nh = r.cls_off[kNumClasses + 1] - r.cls_off[kNumClasses];
-  if ((int)blockIdx.x < nh) {
+  if (bx < nh) {
     s.block = true;
     s.G = kBlock;
     s.gl = threadIdx.x;
-    s.entry = r.cls_off[kNumClasses] + (int)blockIdx.x;
+    s.entry = r.cls_off[kNumClasses] + bx;
     s.active = true;
     return true;
   }
   s.block = false;
-  const int wave = ((int)blockIdx.x - nh) * kWavesPerBlock + (int)(threadIdx.x >> 6);
+  const int wave = (bx - nh) * kWavesPerBlock + (int)(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (wave >= r.wave_off[kNumClasses]) return false;
   int c = 0;
@@ -331,6 +331,9 @@ __device__ __forceinline__ bool group_slot(const GroupRange& r, GroupSlot& s) {
   s.entry = r.cls_off[c] + (wave - r.wave_off[c]) * (64 >> lg) + (lane >> lg);
   s.active = s.entry < r.cls_off[c + 1];
   return true;
+}
+__device__ __forceinline__ bool group_slot(const GroupRange& r, GroupSlot& s) {
+  return group_slot(r, s, (int)blockIdx.x);
 }
 
 // The same mapping for a level kernel, whose smallest group is 2^G0 >= 4 lanes, so that at
@@ -2480,6 +2483,24 @@ __device__ __forceinline__ void pre_cell(const BwdArgs& a, const Slots& sl, int 
   }
 }
 
+// A role of the net that group_slot or step_slot gave, compiled for its group.
+template <bool kGrad, bool kRat, bool kCkpt>
+__device__ __forceinline__ void chain_role(const BwdArgs& a, const Slots& sl, const GroupSlot& gs, float* sh) {
+  if (gs.block || gs.G == 64) chain_net<64, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 32) chain_net<32, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 16) chain_net<16, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else if (gs.G == 8) chain_net<8, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  else chain_net<4, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+}
+template <bool kGrad, bool kRat, bool kCkpt, bool kStream>
+__device__ __forceinline__ void post_role(const BwdArgs& a, const GroupSlot& gs, float* sh) {
+  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 32) post_net<32, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 16) post_net<16, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else if (gs.G == 8) post_net<8, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  else post_net<4, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+}
+
 // One level l >= 1: workgroups [0, n_chain) the chain role of its nets, the rest the cells of the
 // next lower level (`pre`).  The values that the chain's first loads need come first, preloaded
 // into scalar registers.
@@ -2504,11 +2525,40 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step(int n_chain, int nh, int h0
   const LevelRanges r{nh, h0, e0, e1, e2, e3, r0.e4, r0.e5, w1, w2, w3, r0.w4, r0.w5, r0.g0};
   GroupSlot gs;
   if (!step_slot(sb.x, r, gs)) return;
-  if (gs.block || gs.G == 64) chain_net<64, kGrad, kRat, kCkpt>(a, sl, gs, sh);
-  else if (gs.G == 32) chain_net<32, kGrad, kRat, kCkpt>(a, sl, gs, sh);
-  else if (gs.G == 16) chain_net<16, kGrad, kRat, kCkpt>(a, sl, gs, sh);
-  else if (gs.G == 8) chain_net<8, kGrad, kRat, kCkpt>(a, sl, gs, sh);
-  else chain_net<4, kGrad, kRat, kCkpt>(a, sl, gs, sh);
+  chain_role<kGrad, kRat, kCkpt>(a, sl, gs, sh);
+}
+
+// The lowest level of a checkpointing segment: workgroups [0, n_chain) the chain role of its nets,
+// the rest the outputs of the segment's own nets (`outs`), whose sinks the levels above have
+// written and this chain, which writes sinks of earlier segments, leaves alone.  As a launch of
+// their own the outputs made each segment one launch longer than with the fused kernel: gradient
+// steps of 841k pins in segments of 8 levels took 804 us on the device and the host's time for the
+// launches, 774 beside the level (fused 860); in segments of one level 1754 and 1539 (fused 1585).
+template <bool kSnap, bool kGrad, bool kRat, bool kStream>
+__global__ __launch_bounds__(kBlock) void k_bwd_last(int n_chain, const int* __restrict__ sched, GroupRange outs,
+                                                     BwdArgs a, Slots sl, LevelRanges r, int snap_state) {
+  __shared__ float sh[kWavesPerBlock * N_ACC];
+  const SnapBlock sb = snap_block<kSnap>();
+  a.rec = snap_bytes<kSnap>(a.rec, (size_t)snap_state, sb.s);
+  a.wire = snap_bytes<kSnap>(a.wire, (size_t)snap_state, sb.s);
+  a.sink = snap_bytes<kSnap>(a.sink, a.snap.work, sb.s);
+  GroupSlot gs;
+  if (sb.x < n_chain) {
+    if (!step_slot(sb.x, r, gs)) return;
+    chain_role<kGrad, kRat, true>(a, sl, gs, sh);
+    return;
+  }
+  a.x = snap_elems<kSnap>(a.x, a.snap.pins, sb.s);
+  a.y = snap_elems<kSnap>(a.y, a.snap.pins, sb.s);
+  a.at_out = snap_elems<kSnap>(a.at_out, a.snap.pins, sb.s);
+  a.slew_out = snap_elems<kSnap>(a.slew_out, a.snap.pins, sb.s);
+  a.rat_out = snap_elems<kSnap>(a.rat_out, a.snap.pins, sb.s);
+  a.slack_out = snap_elems<kSnap>(a.slack_out, a.snap.pins, sb.s);
+  a.dx = snap_elems<kSnap>(a.dx, a.snap.pins, sb.s);
+  a.dy = snap_elems<kSnap>(a.dy, a.snap.pins, sb.s);
+  if (!group_slot(outs, gs, sb.x - n_chain)) return;
+  gs.entry = gs.active ? sched[gs.entry] : 0;
+  post_role<kGrad, kRat, true, kStream>(a, gs, sh);
 }
 
 // Outputs of every net, after the last level.
@@ -2531,11 +2581,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int*
   GroupSlot gs;
   if (!group_slot(range, gs)) return;
   gs.entry = gs.active ? sched[gs.entry] : 0;
-  if (gs.block || gs.G == 64) post_net<64, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
-  else if (gs.G == 32) post_net<32, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
-  else if (gs.G == 16) post_net<16, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
-  else if (gs.G == 8) post_net<8, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
-  else post_net<4, kGrad, kRat, kCkpt, kStream>(a, gs, sh);
+  post_role<kGrad, kRat, kCkpt, kStream>(a, gs, sh);
 }
 
 // Seeds of the endpoints list[0..n_ep) (every endpoint when list is NULL), and beside them the cells role of the deepest level.
@@ -4122,11 +4168,20 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
 //     12.6k 258 -> 258, 13.5k 587 -> 639, 27k 807 -> 1036;
 //   gradient alone (its slots are half as wide): 3.4k 326 -> 229, 7.4k 511 -> 430, 13.5k
 //     540 -> 493, 22k 948 -> 1069, 27k 712 -> 795.
+// Under checkpointing the line comes sooner.  Whole steps in segments of 1, 3 and 8-10 levels:
+//   with required times: 3.4k nets a level 1606 -> 1602, 1062 -> 1002, 878 -> 804 us; 5.4k 2060 ->
+//     2089, 1365 -> 1321, 1137 -> 1063; 7.3k 2416 -> 2519, 1597 -> 1653, 1309 -> 1317; 9.3k 2955 ->
+//     3100, 1870 -> 1994, 1530 -> 1605;
+//   gradient alone: 5.4k 2016 -> 1985, 1326 -> 1256, 1098 -> 1015; 9.3k 2940 -> 2915, 1815 -> 1830,
+//     1464 -> 1451; 12k (five snapshots) 1585 -> 1569, 1103 -> 1081, 965 -> 927; 15k 1826 -> 1845,
+//     1300 -> 1320, 1143 -> 1165.
 bool split_levels(const sta_graph* g, bool rat) {
   const int64_t per_level = (int64_t)g->n_snap * g->N / std::max(1, g->L);
+  const bool ckpt = g->ckpt_stride > 0;
   // Checkpointed RC trees keep no list of each segment's nets, for their outputs.
-  if (g->ckpt_stride > 0 && g->rc_ranges.empty()) return false;
-  return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= (rat ? 10000 : 16384);
+  if (ckpt && g->rc_ranges.empty()) return false;
+  const int64_t line = rat ? (ckpt ? 6000 : 10000) : (ckpt ? 13000 : 16384);
+  return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= line;
 }
 
 // Whether k_bwd_out writes its outputs as streaming stores.  Those are the slower ones (see post_net),
@@ -4251,10 +4306,11 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
       body(j, d.ep_grp + g->ep_grp_off[q], g->ep_grp_off[q + 1] - g->ep_grp_off[q], lo, hi);
     }
   };
-  auto sweep_split = [&](auto kstart, auto kstep, auto kout) {
+  auto sweep_split = [&](auto kstart, auto kstep, auto klast, auto kout) {
     const bool snap = g->n_snap > 1;
-    // Levels hi - 1 .. lo: their endpoints' seeds beside the deepest level's cells, then level by level.
-    auto levels = [&](const int* list, int n_ep, int lo, int hi) {
+    // Levels hi - 1 .. lo: their endpoints' seeds beside the deepest level's cells, then level by
+    // level, the lowest with a segment's outputs `outs` beside it.
+    auto levels = [&](const int* list, int n_ep, int lo, int hi, const GroupRange* outs) {
       const Slots deepest = hi > lo ? level_slots(g, hi - 1) : Slots{0, 1, 0, 0};
       const unsigned n_seed = (unsigned)((n_ep + kBlock - 1) / kBlock), blocks = n_seed + cell_blocks(deepest);
       if (blocks > 0) {
@@ -4265,14 +4321,20 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
         const GroupRange& r = g->lvl_ranges[l];
         const unsigned chain = range_grid(r);
         const Slots pre = l > lo ? level_slots(g, l - 1) : Slots{0, 1, 0, 0};
-        const unsigned all = chain + cell_blocks(pre);
+        const bool last = outs && l == lo;
+        const unsigned all = chain + (last ? range_grid(*outs) : cell_blocks(pre));
         if (all == 0) continue;
         LaunchTimer t(g, s, STA_K_BWD_LEVEL);
         const int* c = r.cls_off;
         const int* w = r.wave_off;
         const LevelRanges lr{c[kNumClasses + 1] - c[kNumClasses], c[kNumClasses], c[0], c[1], c[2], c[3], c[4], c[5],
                              w[1], w[2], w[3], w[4], w[5], r.g0};
-        kstep<<<snap ? level_grid(g, all) : dim3(all), kBlock, 0, s>>>(
+        const dim3 grid = snap ? level_grid(g, all) : dim3(all);
+        if (last) {
+          klast<<<grid, kBlock, 0, s>>>((int)chain, d.sched_all, *outs, ba, level_slots(g, l), lr, ss);
+          continue;
+        }
+        kstep<<<grid, kBlock, 0, s>>>(
             (int)chain, lr.nh, lr.h0, lr.e0, lr.e1, lr.e2, lr.e3, lr.w1, lr.w2, lr.w3, d.net_off, d.ell, ba,
             level_slots(g, l), pre, lr, ss);
       }
@@ -4284,15 +4346,14 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
       kout<<<snap_grid(g, blocks), kBlock, 0, s>>>(r, d.sched_all, ba, ss);
     };
     if (g->ckpt_stride <= 0) {
-      levels(nullptr, g->E, 1, g->L);
+      levels(nullptr, g->E, 1, g->L, nullptr);
       outputs(g->all_range);
       return;
     }
     // Nets whose sinks hold segment slots give their outputs with their segment, the others (level 0
     // among them; their records are kept too) at the end: the lists of the RC passes.
     segments([&](int j, const int* list, int n_ep, int lo, int hi) {
-      levels(list, n_ep, lo, hi);
-      outputs(g->rc_ranges[(size_t)j + 1]);
+      levels(list, n_ep, lo, hi, &g->rc_ranges[(size_t)j + 1]);
     });
     outputs(g->rc_ranges[0]);
   };
@@ -4300,10 +4361,13 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
     constexpr bool S = decltype(snap)::value, K = decltype(ckpt)::value;
     const bool stream = stream_outputs(g, io, *out);
     if (!grad) sweep_split(k_bwd_start<false, true, K>, k_bwd_step<S, false, true, K>,
+                           stream ? k_bwd_last<S, false, true, true> : k_bwd_last<S, false, true, false>,
                            stream ? k_bwd_out<false, true, K, true> : k_bwd_out<false, true, K, false>);
     else if (rat) sweep_split(k_bwd_start<true, true, K>, k_bwd_step<S, true, true, K>,
+                              stream ? k_bwd_last<S, true, true, true> : k_bwd_last<S, true, true, false>,
                               stream ? k_bwd_out<true, true, K, true> : k_bwd_out<true, true, K, false>);
     else sweep_split(k_bwd_start<true, false, K>, k_bwd_step<S, true, false, K>,
+                     stream ? k_bwd_last<S, true, false, true> : k_bwd_last<S, true, false, false>,
                      stream ? k_bwd_out<true, false, K, true> : k_bwd_out<true, false, K, false>);
   };
   if (split) {

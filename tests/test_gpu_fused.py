@@ -13,7 +13,7 @@ from tests._designs import fanout_design, wide_dag
 
 pytestmark = pytest.mark.gpu
 
-LINE = 16384          # nets a level beyond which every backward is fused
+LINE = 16384          # nets a level beyond which every backward is fused, checkpointed or not
 DESIGNS = {"wide": lambda: wide_dag(n_levels=9, gates_per_level=60, n_pi=16, seed=7),
            "fanout": lambda: fanout_design(via_cell=True),
            "tail": lambda: make_design(scaled_spec(30_000, cfg_id=81, box_um=400.0))}
@@ -41,10 +41,11 @@ def _backward(g, x, y, canonical, kind, levels, fused):
     return {k: v.cpu().numpy() for k, v in o.items()}
 
 
+@pytest.mark.parametrize("stride", [0, 4])
 @pytest.mark.parametrize("canonical", [False, True])
 @pytest.mark.parametrize("form", ["snapshots", "batch"])
 @pytest.mark.parametrize("design", list(DESIGNS))
-def test_fused_levels_equal_split_levels_bitwise(design, form, canonical):
+def test_fused_levels_equal_split_levels_bitwise(design, form, canonical, stride):
     d = DESIGNS[design]()
     one = Graph.from_design(d)
     L = one.levelize()
@@ -57,6 +58,7 @@ def test_fused_levels_equal_split_levels_bitwise(design, form, canonical):
     else:
         many = Graph.batch([one] * n)
         many.levelize()
+    many.set_checkpointing(stride)
     order = one.levelization()["pin_perm"]
     if form == "snapshots":
         xm, ym = (v[:, order] for v in (xs, ys)) if canonical else (xs, ys)
@@ -76,7 +78,7 @@ def test_fused_levels_equal_split_levels_bitwise(design, form, canonical):
         one.set_schedule(sweep, 2, 64)
         many.set_schedule(sweep, 2, 64)
         for kind in KINDS:
-            print(f"fused: {design} {form} x{n} sweep {sweep} canonical {canonical} {kind}", flush=True)
+            print(f"fused: {design} {form} x{n} sweep {sweep} canonical {canonical} stride {stride} {kind}", flush=True)
             got = _backward(many, xm, ym, canonical, kind, L, fused=True)
             for s in (0, n - 1):
                 x1, y1 = (v[s][order] for v in (xs, ys)) if canonical else (xs[s], ys[s])

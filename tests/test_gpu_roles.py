@@ -122,3 +122,21 @@ def test_profile_counts_levels_apart_from_the_output_pass(form):
     g.profile(False)
     assert got["fwd_level"][0] == L - 1 and got["ep_seed"][0] == 1
     assert (got["bwd_level"][0], got["expand"][0]) == ((L, 0) if form == "fused" else (L - 1, 1))
+
+
+@pytest.mark.parametrize("stride", [5, 8, 1000])
+def test_checkpointed_segments_launch_once_a_level(stride):
+    # A segment's outputs ride with its lowest level: no launch more than the fused kernel's, whose level 0
+    # the last output pass replaces.
+    d = make_design(scaled_spec(30_000, cfg_id=84, box_um=400.0))
+    g = Graph.from_design(d)
+    L = g.levelize()
+    g.set_checkpointing(stride)
+    x, y = torch.tensor(d.x, device="cuda"), torch.tensor(d.y, device="cuda")
+    f = g.forward(x, y, gamma=GAMMA)
+    g.profile(True)
+    g.backward(x, y, f, pins=False)
+    ran = g.profile_read()
+    g.profile(False)
+    assert ran["ep_seed"][0] <= 1 + -(-(L - 1) // stride)
+    assert (ran["bwd_level"][0], ran["expand"][0]) == (L - 1, 1)
