@@ -1549,8 +1549,9 @@ __global__ __launch_bounds__(kBlock) void k_ep_values(EpArgs a0, const int* __re
 }
 
 // ---------------------------------------------------------------------------- outputs
-// Streaming store of a per-pin output: written once, read by no later kernel of the sweep,
-// so it bypasses the cache instead of waiting in L2 for the end-of-kernel writeback.
+// Streaming store of a per-pin output: written once, read by no later kernel of the sweep, so it
+// leaves the caches to the state and graph.  A line's pieces then don't meet in L2, so the passes
+// that write nothing but outputs store plainly where the outputs are small (stream_outputs).
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void store_stream(float4* p, const float4 v) {
@@ -1577,6 +1578,7 @@ struct ExpandArgs {
 };
 
 // Per-pin arrival, slew and smoothed arrival from the net records (forward outputs).
+template <bool kStream>
 __global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
   const float4* __restrict__ rec = snap_bytes(a.rec, a.snap.state);
   const float2* __restrict__ wire = snap_bytes(a.wire, a.snap.state);
@@ -1585,8 +1587,10 @@ __global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
   float2* atg_out = snap_elems(a.atg, a.snap.pins);
   GroupSlot gs;
   if (!group_slot(a.range, gs) || !gs.active) return;
-  // Plain stores: scattered streaming ones in original order took 94 us for 841k pins, these 35 us.
-  auto put = [](auto* p, const auto& v) { *p = v; };
+  auto put = [](auto* p, const auto& v) {
+    if (kStream) store_stream(p, v);
+    else *p = v;
+  };
   const int n = a.sched[gs.entry];
   const int p0 = a.net_off[n], p1 = a.net_off[n + 1];
   const float4 c0 = rec[kRecChunks * (size_t)n], c1 = rec[kRecChunks * (size_t)n + 1],
@@ -1599,7 +1603,7 @@ __global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
     if (at_out) put(at_out + q, make_float4(at.x + w.x, at.y + w.x, at.z + w.x, at.w + w.x));
     if (slew_out)
       put(slew_out + q,
-                   make_float4(sink_slew(sl.x, w.y), sink_slew(sl.y, w.y), sink_slew(sl.z, w.y), sink_slew(sl.w, w.y)));
+          make_float4(sink_slew(sl.x, w.y), sink_slew(sl.y, w.y), sink_slew(sl.z, w.y), sink_slew(sl.w, w.y)));
     if (atg_out) put(atg_out + q, make_float2(ag.x + w.x, ag.y + w.x));
   }
 }
@@ -4067,6 +4071,21 @@ sta_status launch_backward_si(sta_graph* g, const float* x, const float* y, cons
   return STA_OK;
 }
 
+// Whether an output pass of `float4s` arrays of 16 bytes a pin (halves: smoothed arrivals) writes them as
+// streaming stores.  Plain ones let a line's pieces, from a net's sinks and its driver, meet in L2, but
+// push the state and graph that the next kernels and calls read out of the 256 MB last-level
+// cache: streaming pays in canonical order, where stores cover whole lines, once the outputs
+// fill about half of that cache.  Repeated on one placement, plain and streaming, us:
+//   full steps (four arrays): 52 MB 438 and 448, 77 MB 525 and 540, 102 MB 618 and 633, 122 MB 693
+//     and 684, 134 MB 761 and 742, 160 MB 851 and 824; 3 snapshots of 96 MB 550 and 548, 5 of 128 MB 576
+//     and 578;
+//   forward with arrivals, slews and smoothed arrivals: 80 MB 323 and 324, 100 MB 363 and 359, 128 MB
+//     460 and 421, 240 MB 702 and 679; 4 snapshots of 129 MB 350 and 338, 8 of 258 MB 569 and 505;
+//   the same in original order: 8 snapshots of 32 MB 169 and 217, of 258 MB 843 and 1338.
+bool stream_outputs(const sta_graph* g, const int* io, double float4s) {
+  return io == nullptr && 16.0 * float4s * g->P * g->n_snap > 120.0 * (1 << 20);
+}
+
 sta_status launch_forward(sta_graph* g, const float* x, const float* y, const sta_fwd_out* out, uint32_t flags,
                           float gamma_ps, hipStream_t s) {
   if (g->lanes_kernels()) return launch_forward_si(g, x, y, out, flags, gamma_ps, s);
@@ -4160,7 +4179,9 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
     ExpandArgs xa{d.net_off, io, d.sched_all, g->all_range, rec, wire, reinterpret_cast<float4*>(out->at),
                   reinterpret_cast<float4*>(out->slew), reinterpret_cast<float2*>(out->atg), sn};
     LaunchTimer t(g, s, STA_K_EXPAND);
-    k_expand<<<snap_grid(g, range_grid(g->all_range)), kBlock, 0, s>>>(xa);
+    const dim3 grid = snap_grid(g, range_grid(g->all_range));
+    if (stream_outputs(g, io, !!out->at + !!out->slew + 0.5 * !!out->atg)) k_expand<true><<<grid, kBlock, 0, s>>>(xa);
+    else k_expand<false><<<grid, kBlock, 0, s>>>(xa);
   }
   if (g->profiling) end_run(g, s);
   hipError_t e = hipGetLastError();
@@ -4191,17 +4212,6 @@ bool split_levels(const sta_graph* g, bool rat) {
   if (ckpt && g->rc_ranges.empty()) return false;
   const int64_t line = rat ? (ckpt ? 6000 : 10000) : (ckpt ? 13000 : 16384);
   return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= line;
-}
-
-// Whether k_bwd_out writes its outputs as streaming stores.  Those are the slower ones (see post_net),
-// but leave the 256 MB last-level cache to the state and graph that the next call reads: worth it
-// once the outputs fill most of that cache, in canonical order, where stores cover whole lines.
-// A step repeated on one placement, plain and streaming: 2.6M pins (187 MB) 883 and 838 us; 108k pins in 8
-// snapshots (62 MB) 302 and 310; 637k pins (46 MB) 312 and 317; 414k pins with RC trees in original order 400
-// and 428.
-bool stream_outputs(const sta_graph* g, const int* io, const sta_bwd_out& out) {
-  const int64_t bytes = (int64_t)g->n_snap * g->P * 16 * (!!out.at + !!out.slew + !!out.rat + !!out.slack);
-  return io == nullptr && bytes > (128ll << 20);
 }
 
 // Workgroups of the cells role over one level.
@@ -4368,7 +4378,7 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
   };
   auto sweep = [&](auto snap, auto ckpt) {
     constexpr bool S = decltype(snap)::value, K = decltype(ckpt)::value;
-    const bool stream = stream_outputs(g, io, *out);
+    const bool stream = stream_outputs(g, io, !!out->at + !!out->slew + !!out->rat + !!out->slack);
     if (!grad) sweep_split(k_bwd_start<false, true, K>, k_bwd_step<S, false, true, K>,
                            stream ? k_bwd_last<S, false, true, true> : k_bwd_last<S, false, true, false>,
                            stream ? k_bwd_out<false, true, K, true> : k_bwd_out<false, true, K, false>);

@@ -2,6 +2,8 @@
 required times or without the gradient; and RC-tree chunks at the edges of their packing."""
 from __future__ import annotations
 
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -140,3 +142,55 @@ def test_checkpointed_segments_launch_once_a_level(stride):
     g.profile(False)
     assert ran["ep_seed"][0] <= 1 + -(-(L - 1) // stride)
     assert (ran["bwd_level"][0], ran["expand"][0]) == (L - 1, 1)
+
+
+STREAM = 120 << 20        # output bytes beyond which canonical output passes write streaming stores
+
+
+@pytest.mark.parametrize("names,per_pin", [(("at", "slew", "atg"), 40), (("slew",), 16)])
+def test_forward_outputs_streamed_and_plain_equal_bitwise(names, per_pin):
+    # Snapshots on both sides of the line in canonical order, and in original order, always plain.
+    d = make_design(scaled_spec(30_000, cfg_id=85, box_um=400.0))
+    n = STREAM // (per_pin * d.n_pins)
+    g = Graph.from_design(d)
+    g.levelize()
+    perm = g.levelization()["pin_perm"]
+    ref = None
+    for S, canonical in ((1, True), (n, True), (n + 1, True), (n + 1, False)):
+        g.set_snapshots(S)
+        x, y = ((v[perm] if canonical else v)[None].repeat(S, 0) for v in (d.x, d.y))
+        x, y = (torch.tensor(v[0] if S == 1 else v, device="cuda") for v in (x, y))
+        out = {k: torch.full(((S,) if S > 1 else ()) + (d.n_pins, 2 if k == "atg" else 4), float("nan"), device="cuda")
+               for k in names}
+        g.forward(x, y, gamma=GAMMA, canonical=canonical, out=out)
+        torch.cuda.synchronize()
+        got = {k: v.cpu().numpy().reshape(S, d.n_pins, -1)[[0, S - 1]] for k, v in out.items()}
+        if not canonical:
+            got = {k: v[:, perm] for k, v in got.items()}
+        ref = ref or got
+        for k in names:
+            assert np.array_equal(got[k], ref[k][[0, -1]], equal_nan=True), (S, canonical, k)
+
+
+@pytest.mark.slow
+def test_backward_outputs_streamed_and_plain_equal_bitwise():
+    # 134 MB of outputs of deep, narrow levels, which stay split also under checkpointing: streamed
+    # in canonical order by the output pass and by a segment's lowest level, plain in original order.
+    d = make_design(dataclasses.replace(scaled_spec(2_100_000, cfg_id=86, box_um=3000.0), n_levels=112))
+    assert 64 * d.n_pins > STREAM
+    g = Graph.from_design(d)
+    L = g.levelize()
+    assert d.n_nets // L < 6000
+    perm = g.levelization()["pin_perm"]
+    plain = _sweep(g, torch.tensor(d.x, device="cuda"), torch.tensor(d.y, device="cuda"))
+    x, y = torch.tensor(d.x[perm], device="cuda"), torch.tensor(d.y[perm], device="cuda")
+    for stride in (0, 16):
+        g.set_checkpointing(stride)
+        f = g.forward(x, y, gamma=GAMMA, canonical=True)
+        g.profile(True)
+        o = g.backward(x, y, f)
+        ran = g.profile_read()
+        g.profile(False)
+        assert (ran["bwd_level"][0], ran["expand"][0]) == (L - 1, 1)
+        for k, v in o.items():
+            assert np.array_equal(v.cpu().numpy(), plain[k][perm], equal_nan=True), (stride, k)
