@@ -731,42 +731,40 @@ sta_status sta_levelize(sta_graph* g, int32_t* n_levels_out) {
         }
       }
       // Chunks of whole nets for the LDS kernels (depth -1: a net too big for one, left to the
-      // fallback kernel).
-      g->tree_blk_net.assign(1, 0);
-      g->tree_blk_depth.clear();
+      // fallback kernel), in both sizes that the snapshot count may call for (tree_chunks_of).
       g->tree_big.clear();
-      // A chunk is a chain of barriers, so small chunks end sooner as long as they all fit the chip
-      // at once (about four workgroups a CU): RC and its adjoint over 100k pins take 14.5 + 15.7 us
-      // in chunks of 256 pins, 16 + 16 of 512, 21 + 21 of 1024; 415k pins 22 + 23, 19 + 21, 25 + 26;
-      // 2.6M pins 66 + 76, 58 + 68, 56 + 74.  A larger net takes a chunk of its own.
-      const int pack = P <= (1 << 18) ? 256 : 512;
-      int pins = 0, depth = 0;
-      for (int i = 0; i < N; ++i) {
-        const int np = g->c_net_off[i + 1] - g->c_net_off[i];
-        int dn = 0;
-        for (int q = g->c_net_off[i]; q < g->c_net_off[i + 1]; ++q) dn = std::max(dn, g->c_tree_node[q].x);
-        if (np > kTreeChunk) {
-          if (i > g->tree_blk_net.back()) {
-            g->tree_blk_depth.push_back(depth);
-            g->tree_blk_net.push_back(i);
+      for (int k = 0; k < 2; ++k) {
+        TreeChunks& t = g->tree_chunks[k];
+        t.net.assign(1, 0);
+        t.depth.clear();
+        int pins = 0, depth = 0;
+        for (int i = 0; i < N; ++i) {
+          const int np = g->c_net_off[i + 1] - g->c_net_off[i];
+          int dn = 0;
+          for (int q = g->c_net_off[i]; q < g->c_net_off[i + 1]; ++q) dn = std::max(dn, g->c_tree_node[q].x);
+          if (np > kTreeChunk) {
+            if (i > t.net.back()) {
+              t.depth.push_back(depth);
+              t.net.push_back(i);
+            }
+            if (k == 0) g->tree_big.push_back(i);
+            t.depth.push_back(-1);
+            t.net.push_back(i + 1);
+            pins = depth = 0;
+            continue;
           }
-          g->tree_big.push_back(i);
-          g->tree_blk_depth.push_back(-1);
-          g->tree_blk_net.push_back(i + 1);
-          pins = depth = 0;
-          continue;
+          if (pins > 0 && pins + np > kTreePack[k]) {
+            t.depth.push_back(depth);
+            t.net.push_back(i);
+            pins = depth = 0;
+          }
+          pins += np;
+          depth = std::max(depth, dn);
         }
-        if (pins > 0 && pins + np > pack) {
-          g->tree_blk_depth.push_back(depth);
-          g->tree_blk_net.push_back(i);
-          pins = depth = 0;
+        if (N > t.net.back()) {
+          t.depth.push_back(depth);
+          t.net.push_back(N);
         }
-        pins += np;
-        depth = std::max(depth, dn);
-      }
-      if (N > g->tree_blk_net.back()) {
-        g->tree_blk_depth.push_back(depth);
-        g->tree_blk_net.push_back(N);
       }
     }
     // Level 0 holds exactly the PI-driven nets; every later net is driven by a cell.
@@ -1022,8 +1020,11 @@ sta_status sta_graph_upload(sta_graph* g) {
       (!g->sink_base.empty() && ((s = up(d.sink_base, g->sink_base)) || (s = up(d.ep_sslot, g->ep_sslot)))) ||
       (g->ckpt_stride > 0 && ((s = up(d.rec_loc, g->rec_loc)) || (s = up(d.ep_grp, g->ep_grp)))) ||
       (!g->c_parent.empty() && ((s = up(d.parent, g->c_parent)) || (s = up(d.tree_order, g->c_tree_order)) ||
-                                (s = up(d.tree_node, g->c_tree_node)) || (s = up(d.tree_blk_net, g->tree_blk_net)) ||
-                                (s = up(d.tree_blk_depth, g->tree_blk_depth)) || (s = up(d.tree_big, g->tree_big)))) ||
+                                (s = up(d.tree_node, g->c_tree_node)) || (s = up(d.tree_big, g->tree_big)) ||
+                                (s = up(d.tree_blk_net[0], g->tree_chunks[0].net)) ||
+                                (s = up(d.tree_blk_depth[0], g->tree_chunks[0].depth)) ||
+                                (s = up(d.tree_blk_net[1], g->tree_chunks[1].net)) ||
+                                (s = up(d.tree_blk_depth[1], g->tree_chunks[1].depth)))) ||
       (s = up(d.lut_grid, grid))) {
     free_device(g);
     return s;

@@ -20,7 +20,8 @@ constexpr int kLutKeysAt = kLutCells;      // in the tables' device array: the b
 constexpr int kLutCoefAt = kLutCells + 3;  // three float4) follow the grid, then the coefficients
 constexpr int kFlatG0Default = 2;    // flat kernels (RC, outputs): smallest group 4 lanes
 constexpr int kSweepG0Default = 2;   // level kernels: smallest backward group 4 lanes (one per condition)
-constexpr int kTreeChunk = 1024;     // RC trees: most pins of whole nets swept by one workgroup in LDS
+constexpr int kTreeChunk = 1024;     // RC trees: most pins of whole nets swept by one workgroup in LDS,
+constexpr int kTreePack[2] = {256, 512};   // and the pins up to which nets share one (tree_chunks_of)
 constexpr int kSiHeavy = 12;         // snapshot-inner layout: nets with more sinks take a whole
                                      // workgroup for up to 64 snapshots,
 constexpr int kSiHuge = 128;         // nets with more than this a workgroup per 8 snapshots (RC,
@@ -80,6 +81,11 @@ struct WorkLayout {
   size_t total;
 };
 
+// Chunks of whole nets: chunk b holds nets [net[b], net[b + 1]), depth[b] its deepest node's depth.
+struct TreeChunks {
+  std::vector<int> net, depth;
+};
+
 struct DeviceGraph {
   int device = -1;
   std::vector<void*> allocs;
@@ -97,8 +103,8 @@ struct DeviceGraph {
   int* parent = nullptr;       // [P] RC trees only: canonical parent pin, -1 at drivers
   int* tree_order = nullptr;   // [P] RC trees only: each net's pins in breadth-first order
   int4* tree_node = nullptr;   // [P] RC trees only: {depth, first child position, children, 0}
-  int* tree_blk_net = nullptr;    // RC trees only: chunk net ranges
-  int* tree_blk_depth = nullptr;  // RC trees only: deepest depth of each chunk
+  int* tree_blk_net[2] = {};      // RC trees only: chunk net ranges, by chunk size
+  int* tree_blk_depth[2] = {};    // RC trees only: deepest depth of each chunk
   int* tree_big = nullptr;        // RC trees only: nets over the chunk size
   float4* lut_grid = nullptr;  // [36] {x_i, 1/(x_i+1 - x_i), y_j, 1/(y_j+1 - y_j)}, then LutKeys
   float4* lut_coef = nullptr;  // [n_arcs * 2 * 36 * 2] bilinear coefficients {a, b, c, d}; in one
@@ -144,8 +150,7 @@ struct sta_graph {
                                                // driver); each net's pins in breadth-first order
   std::vector<int4> c_tree_node;               // RC trees, per canonical pin: {depth, breadth-first
                                                // position of the first child, children, 0}
-  std::vector<int> tree_blk_net, tree_blk_depth;  // RC trees: chunks of whole nets of at most
-                                               // kTreeChunk pins (net ranges, deepest depth)
+  sta::TreeChunks tree_chunks[2];              // RC trees: chunks of whole nets, by chunk size
   std::vector<int> tree_big;                   // RC trees: nets over kTreeChunk pins
   std::vector<sta::GroupRange> lvl_ranges;   // per level
   sta::GroupRange all_range{};                 // all nets

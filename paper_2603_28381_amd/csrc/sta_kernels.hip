@@ -4071,6 +4071,14 @@ sta_status launch_backward_si(sta_graph* g, const float* x, const float* y, cons
   return STA_OK;
 }
 
+// Which of an RC-tree graph's chunk sizes (kTreePack) a sweep takes.  A chunk is a chain of barriers,
+// so small chunks end sooner as long as all snapshots' fit the chip at once (about four
+// workgroups a CU).  RC and its adjoint, in chunks of 256, 512 and 1024 pins: 100k pins 14.5 + 15.7 us,
+// 16 + 16, 21 + 21; 8 snapshots of 20k 13.7 + 14.2, 14.7 + 15.6, 18.4 + 19.7; 415k pins 22 + 23, 19 + 21,
+// 25 + 26; 4 of 100k 20 + 22, 18 + 20, 22 + 23; 24 of 100k 56 + 68, 45 + 56, 47 + 66; 16 of 200k 68 + 87,
+// 56 + 73, 59 + 72; 2.6M pins 66 + 76, 58 + 68, 56 + 74.  A larger net takes a chunk of its own.
+int tree_chunks_of(const sta_graph* g) { return (int64_t)g->n_snap * g->P <= 1 << 18 ? 0 : 1; }
+
 // Whether an output pass of `float4s` arrays of 16 bytes a pin (halves: smoothed arrivals) writes them as
 // streaming stores.  Plain ones let a line's pieces, from a net's sinks and its driver, meet in L2, but
 // push the state and graph that the next kernels and calls read out of the 256 MB last-level
@@ -4099,11 +4107,11 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
 
   const Snap sn = snap_of(g);
   const bool tree = !g->c_parent.empty();
-  const int n_chunks = (int)g->tree_blk_depth.size(), n_big = (int)g->tree_big.size();
+  const int ck = tree_chunks_of(g), n_chunks = (int)g->tree_chunks[ck].depth.size(), n_big = (int)g->tree_big.size();
   RcArgs ra{d.net_off, d.pin_cap, x, y, io, d.sched_all, g->all_range, wire, load, rec, g->N0, g->N,
             g->cons.r_per_um, g->cons.c_per_um, g->cons.pi_at, g->cons.pi_slew, sn, d.parent, d.tree_order,
-            tree ? reinterpret_cast<float4*>(sb + g->state.tree) : nullptr, d.tree_node, d.tree_blk_net,
-            d.tree_blk_depth, d.tree_big, n_big, n_chunks, d.sink_base};
+            tree ? reinterpret_cast<float4*>(sb + g->state.tree) : nullptr, d.tree_node, d.tree_blk_net[ck],
+            d.tree_blk_depth[ck], d.tree_big, n_big, n_chunks, d.sink_base};
   // With checkpointing the wire values share slots like the sink workspace: the RC stage runs
   // in passes (lane groups), the kept nets' here and each segment's before its levels.
   const bool rc_passes = !g->rc_ranges.empty();
@@ -4406,12 +4414,14 @@ sta_status launch_backward(sta_graph* g, const float* x, const float* y, const s
   }
   if (grad && tree && (out->dx || out->dy)) {
     // The Elmore adjoint through each net's tree, from the sweep's per-sink adjoints.
+    const int ck = tree_chunks_of(g);
     const TreeAdjArgs ta{d.net_off, d.parent, d.tree_order, io, x, y,
                          reinterpret_cast<const float4*>(sb + g->state.tree),
                          reinterpret_cast<const float2*>(wb + g->work.tree_adj),
                          reinterpret_cast<float4*>(wb + g->work.tree_bar), out->dx, out->dy, g->N,
-                         g->cons.r_per_um, g->cons.c_per_um, snap_of(g), d.tree_node, d.tree_blk_net,
-                         d.tree_blk_depth, d.tree_big, (int)g->tree_big.size(), (int)g->tree_blk_depth.size()};
+                         g->cons.r_per_um, g->cons.c_per_um, snap_of(g), d.tree_node, d.tree_blk_net[ck],
+                         d.tree_blk_depth[ck], d.tree_big, (int)g->tree_big.size(),
+                         (int)g->tree_chunks[ck].depth.size()};
     LaunchTimer t(g, s, STA_K_RC_ADJOINT);
     if (ta.n_chunks > 0) k_rc_tree_adjoint_chunk<<<snap_grid(g, (unsigned)ta.n_chunks), kBlock, 0, s>>>(ta);
     if (ta.n_list > 0)

@@ -194,3 +194,25 @@ def test_backward_outputs_streamed_and_plain_equal_bitwise():
         assert (ran["bwd_level"][0], ran["expand"][0]) == (L - 1, 1)
         for k, v in o.items():
             assert np.array_equal(v.cpu().numpy(), plain[k][perm], equal_nan=True), (stride, k)
+
+
+@pytest.mark.parametrize("S", [8, 9])
+def test_tree_chunks_of_both_sizes_equal_one_call_bitwise(S):
+    # 31k pins alone and in 8 snapshots (below 2^18) take the small chunks, in 9 the large; one net
+    # between the two sizes, one over the largest (the fallback kernel).
+    from gen.netlist import heap_trees
+    designs = [heap_trees(make_design(scaled_spec(27_000, cfg_id=87, box_um=300.0)))]
+    designs += [heap_trees(fanout_design(n_sinks=n, via_cell=True, n_buf=20)) for n in (299, 1030)]
+    one = Graph.batch([Graph.from_design(d) for d in designs])
+    one.levelize()
+    P = sum(d.n_pins for d in designs)
+    assert 8 * P <= 1 << 18 < 9 * P
+    many = Graph.batch([Graph.from_design(d) for d in designs])
+    many.levelize()
+    many.set_snapshots(S)
+    x, y = (np.concatenate([getattr(d, k) for d in designs]).astype(np.float32) for k in "xy")
+    ref = _sweep(one, torch.tensor(x, device="cuda"), torch.tensor(y, device="cuda"))
+    got = _sweep(many, *(torch.tensor(v[None].repeat(S, 0), device="cuda") for v in (x, y)))
+    for k in ref:
+        for s in (0, S - 1):
+            assert np.array_equal(got[k][s], ref[k], equal_nan=True), (s, k)
