@@ -185,9 +185,9 @@ struct sta_graph {
   // The per-sink wire values follow the same slots, so the RC stage runs in passes: the
   // nets with kept slots once before the sweep (rc_ranges[0]), the other nets of segment j
   // before each forward or recomputed pass over it (rc_ranges[1 + j]); rc_sched lists the
-  // nets of each pass by lane-group class and takes sched_all's place on the device (the
-  // kernels that read sched_all otherwise do not run under checkpointing).  rc_seg: each
-  // net's pass (-1 kept, else j).
+  // nets of each pass by lane-group class and takes sched_all's place on the device (under
+  // checkpointing the backward's outputs are written over the same ranges, and no kernel
+  // reads the whole list).  rc_seg: each net's pass (-1 kept, else j).
   std::vector<int> rc_seg, rc_sched;
   std::vector<sta::GroupRange> rc_ranges;
   sta::StateLayout state{};

@@ -24,7 +24,8 @@
 //    (no atomics, Sec. 3.1.1).
 //  * The one-pass RC kernel and the output passes use groups from 4 lanes.
 // The backward level runs these steps side by side on workgroups of their own (k_bwd_step) with
-// per-pin outputs in one pass at the end; wide levels run them fused (k_bwd_level).
+// per-pin outputs in one pass at the end (under checkpointing beside each segment's lowest
+// level); wide levels run them fused (k_bwd_level).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -1138,8 +1139,8 @@ __device__ __forceinline__ LutKeys lut_keys_at(const float4* lut) {
 // come from memory (430 ns) unless something has just read them.  Extra workgroups of the
 // level before read them into the L2 that the level will look in: workgroups go to the 8 XCDs
 // round-robin, so the prefetching ones start at a multiple of 8, and the b-th takes the cells
-// of the next launch's b-th.  Sweeps of 63k and 841k pins 199 -> 194 and 253 -> 242 us (0.18 us a
-// level); started at another offset (another XCD's L2) 255 us.
+// of the next launch's b-th (at another offset, another XCD's L2, nothing is gained).  A level of 63k
+// pins takes 2.68 us instead of 2.78, of 200k 2.68 instead of 2.82.
 __host__ __device__ inline int level_blocks(int cells, int lanes) { return (cells * lanes + kBlock - 1) / kBlock; }
 __host__ __device__ inline int prefetch_block(int cells) { return (level_blocks(cells, kCellLanes) + 7) & ~7; }
 __device__ __forceinline__ void fwd_prefetch(const int4* __restrict__ ell, const float* __restrict__ loads, int base,
@@ -2143,7 +2144,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level(int nh, int h0, int e0, in
 //  * chain: the net step's reductions and the cell step as one multiply-add per input, in
 //    place in those slots: the only part that the next level waits for;
 //  * outputs (post): per-pin outputs and the Elmore adjoint, from the same sinks, in one pass
-//    after the last level.
+//    after the last level, or for a checkpointing segment beside its lowest (k_bwd_last).
 // A level of one design holds about one wave per SIMD, so that its time is the instruction
 // chain and the dependent loads of one wave, not bytes: in one wave the lookups (three round
 // trips), reductions and outputs took 6.1 us a level at 2.6M pins and 5.5 at 68k.  The roles timed
@@ -2160,8 +2161,8 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level(int nh, int h0, int e0, in
 // and {C_r, C_f} (d slew / d slew over the sink's slew, of the worst-slew arc), by output
 // transition; under checkpointing, where drivers have no slot and records may be written, they
 // take words of the net's record that no kernel reads: U and V the last two of its early
-// chunks, C the last of its late ones.  Every value is computed by the operations of k_bwd_level in the same order, so
-// both give the same bits.
+// chunks, C the last of its late ones.  Every value is computed by the operations of
+// k_bwd_level in the same order, so both give the same bits.
 
 // Which net a thread serves, as level_slot, with the smallest group 2^g0 known at run time.
 struct LevelRanges {
@@ -2597,7 +2598,8 @@ __global__ __launch_bounds__(kBlock) void k_bwd_out(GroupRange range, const int*
   post_role<kGrad, kRat, kCkpt, kStream>(a, gs, sh);
 }
 
-// Seeds of the endpoints list[0..n_ep) (every endpoint when list is NULL), and beside them the cells role of the deepest level.
+// Seeds of the endpoints list[0..n_ep) (every endpoint when list is NULL), and beside them the cells
+// role of the deepest level.
 template <bool kGrad, bool kRat, bool kCkpt>
 __global__ __launch_bounds__(kBlock) void k_bwd_start(EpArgs ea, const int* __restrict__ list, int n_ep, int n_seed,
                                                       BwdArgs a, Slots pre, int snap_state) {
@@ -3039,7 +3041,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_level_cte(int lo, int hi, Slots 
 // backward the schedule's lane_block, 256, 512 or 1024) whose threads split the sinks and
 // meet in LDS in thread order.  The light nets' waves come in workgroups of the same size:
 // smaller workgroups let a CU start new waves sooner after its slowest one, larger ones give
-// a heavy net more threads per snapshot.
+// a heavy net more threads per snapshot.  The backward level takes 19.7, 20.5 and 26.6 us with 256,
+// 512 and 1024 threads at 64 snapshots of 841k pins, 11.7, 12.2 and 15.2 at 64 of 108k, 13.3, 13.4
+// and 18.5 at 16 of 841k: sta_tune picks, the schedule's default stays in the middle.
 constexpr int kSiRcBlock = 256;
 
 struct SiLane {
@@ -3884,7 +3888,8 @@ void fwd_narrow_launch(dim3 grid, bool snap, hipStream_t s, const Slots& sl, int
                                                          fa);
 }
 
-// Levels of more cells gain nothing from the prefetch (2.6M pins, 7.3k cells: 899 -> 903 us).
+// Levels of more cells gain little from the prefetch (7.3k cells, 2.5M pins: 3.05 -> 3.01 us a level)
+// or lose (9.3k, 3.5M pins: 3.39 -> 3.53).
 constexpr int kPrefetchCells = 5000;
 
 // `next`: the level launched after this one (no cells: none).
