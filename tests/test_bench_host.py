@@ -51,3 +51,16 @@ def test_schedule_flags_reject_unsupported_values():
         with pytest.raises(SystemExit):
             bench.main(argv)
     assert callable(bench.snapshot_graph_only)
+
+
+def test_split_backward_is_priced_by_its_own_kernels():
+    # With an output pass in the profile, levels and outputs have models of their own; without, one.
+    d = make_design(CFG0)
+    alg = bench.algorithmic_bytes(d, O.levelize(d).level)
+    quiet = {k: (0, 0.0) for k in ("rc", "fwd_level", "ep_partial", "ep_final", "ep_seed", "recompute", "rc_adjoint")}
+    L = len(alg["bwd_level"])
+    split, top = bench.kernel_table(dict(quiet, bwd_level=(L - 1, 1.0), expand=(1, 0.5)), alg, 1)
+    assert split["bwd_level"]["alg_bytes_per_step"] == alg["bwd_step"].sum() and len(alg["bwd_step"]) == L - 1
+    assert split["expand"]["alg_bytes_per_step"] == alg["bwd_out"][0] and top["kernel"] == "bwd_level"
+    fused, _ = bench.kernel_table(dict(quiet, bwd_level=(L, 1.0), expand=(0, 0.0)), alg, 1)
+    assert fused["bwd_level"]["alg_bytes_per_step"] == alg["bwd_level"].sum() and "expand" not in fused
