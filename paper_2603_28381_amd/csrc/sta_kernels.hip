@@ -4211,19 +4211,23 @@ sta_status launch_forward(sta_graph* g, const float* x, const float* y, const st
 //     12.6k 258 -> 258, 13.5k 587 -> 639, 27k 807 -> 1036;
 //   gradient alone (its slots are half as wide): 3.4k 326 -> 229, 7.4k 511 -> 430, 13.5k
 //     540 -> 493, 22k 948 -> 1069, 27k 712 -> 795.
-// Under checkpointing the line comes sooner.  Whole steps in segments of 1, 3 and 8-10 levels:
+// Under checkpointing the line comes sooner, and for short segments sooner still.  Whole steps, fused ->
+// split, in segments of 1, 3 and 6-10 levels:
 //   with required times: 3.4k nets a level 1606 -> 1602, 1062 -> 1002, 878 -> 804 us; 5.4k 2060 ->
-//     2089, 1365 -> 1321, 1137 -> 1063; 7.3k 2416 -> 2519, 1597 -> 1653, 1309 -> 1317; 9.3k 2955 ->
-//     3100, 1870 -> 1994, 1530 -> 1605;
+//     2089, 1365 -> 1321, 1137 -> 1063; 6.1k in original order 2557 -> 2777, 1725 -> 1740, 1465 -> 1365;
+//     6.7k (two snapshots) 1741 -> 1757, 1182 -> 1157, 1004 -> 950; 7.3k 2416 -> 2519, 1597 -> 1653,
+//     1309 -> 1317; 8.9k (two snapshots) 2005 -> 2106, 1378 -> 1417, 1167 -> 1172; 10.3k (five) 1443 ->
+//     1520, 1000 -> 1060, 872 -> 910;
 //   gradient alone: 5.4k 2016 -> 1985, 1326 -> 1256, 1098 -> 1015; 9.3k 2940 -> 2915, 1815 -> 1830,
 //     1464 -> 1451; 12k (five snapshots) 1585 -> 1569, 1103 -> 1081, 965 -> 927; 15k 1826 -> 1845,
 //     1300 -> 1320, 1143 -> 1165.
 bool split_levels(const sta_graph* g, bool rat) {
   const int64_t per_level = (int64_t)g->n_snap * g->N / std::max(1, g->L);
-  const bool ckpt = g->ckpt_stride > 0;
+  const int stride = g->ckpt_stride;
   // Checkpointed RC trees keep no list of each segment's nets, for their outputs.
-  if (ckpt && g->rc_ranges.empty()) return false;
-  const int64_t line = rat ? (ckpt ? 6000 : 10000) : (ckpt ? 13000 : 16384);
+  if (stride > 0 && g->rc_ranges.empty()) return false;
+  int64_t line = rat ? 10000 : 16384;
+  if (stride > 0) line = rat ? (stride >= 4 ? 7500 : 5000) : 13000;
   return g->sched_cfg.level_scheme == STA_LEVEL_GROUPS && per_level <= line;
 }
 
